@@ -9,9 +9,8 @@
 // N = 16 voxels along x, K = 2 taps x 16 input channels per instruction (27 taps padded to 28).
 // A workgroup stages its input tile (halo 1) in LDS with 16 channels per voxel and each wave
 // accumulates 16-voxel rows.  The same kernel runs the backward data pass with flipped,
-// transposed weights.  Weight gradients are a deterministic two-stage reduction on the vector
-// ALUs (per-workgroup partial sums, then a fixed-order sum).  Optimiser: Adam on FP32 master
-// weights.
+// transposed weights.  Weight gradients are a deterministic two-stage reduction (per-workgroup
+// partial sums on the matrix cores, then a fixed-order sum).  Optimiser: Adam on FP32 master weights.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -330,128 +329,199 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
 }
 
 // ------------------------------------------------------------------------------------------
-// weight gradient: dW[co][ci][tap] = sum_v X[v + off(tap)][ci] G[v][co], dB[co] = sum_v G[v][co]
-// Each block accumulates its tiles (grid-stride over tiles) in registers, then writes one row of
-// partial sums; a second kernel adds the rows in a fixed order.  Work item = (co, ci) pair x row
-// group; tile = 16 (x) x 4 (y) x 4 (z) voxels staged as FP32 in LDS, channel-major.
+// weight gradient on the matrix cores: dW[co][ci][tap] = sum_v X[v + off(tap)][ci] G[v][co],
+// dB[co] = sum_v G[v][co], with bf16 X and G (exact products) and FP32 accumulation.
+//
+// One v_mfma_f32_16x16x32_bf16 contracts 32 voxels of a row: A = G (M = 16 output channels), B = X
+// (N = 16 input channels), one accumulator per tap (27, and one for the biases with B = 1).  Both
+// operands need consecutive voxels per lane while the arrays are channels-last, so they are read
+// from LDS with the transposing ds_read_b64_tr_b16: a tap's x offset is then only a row offset.  A
+// workgroup owns tiles of 32 (x) x 4 x 4 X rows (wave w: plane w); an X row in registers serves its
+// nine G rows (y and z neighbours), which keeps the LDS reads at 0.2 KB per matrix instruction, and
+// the row pairs need no halo work: X outside the grid contributes nothing.  Layers with 2 input
+// channels or 1 output channel run with the other channels zero in LDS.
+//
+// The arrays read once take 28 us for 16 -> 16 channels at 128^3 and the matrix instructions 12 us;
+// the vector-ALU form this replaced took 2335 us there (16 -> 1: 298 us, 2 -> 16: 128 us), this one
+// 63 (38, 40) us.  What bounds it is the latency of a tile (fetch, two barriers, 112 matrix
+// instructions in one wave per SIMD): 85 us without the register prefetch of the next tile at two
+// workgroups per CU, 225 us with both (the prefetch spills).
+//
+// Each workgroup sums its tiles (grid stride) in registers and writes one row of partial sums (its
+// waves added in a fixed order); a second kernel adds the rows in a fixed order in FP64.
 
-constexpr int WTX = 16, WTY = 4, WTZ = 4;
-constexpr int WSX = 20, WSY = WTY + 2, WSZ = WTZ + 2;  // x staged as -2..17 (16-byte aligned rows)
+constexpr int WTX = 32, WTY = 4, WTZ = 4;      // X rows of a tile: WTY x WTZ, 32 voxels long
+constexpr int WXV = (WTX + 2) * WTY * WTZ;     // staged X voxels (one-voxel halo in x)
+constexpr int WGV = WTX * (WTY + 2) * (WTZ + 2);  // staged G voxels (one-row halo in y and z)
+constexpr int WACC = 28;                       // accumulators: 27 taps and the biases
+
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+// The 8 voxels 8 (lane >> 4) + j of a 32-voxel row at p (channels-last, 16 channels), channel lane & 15.
+__device__ __forceinline__ bf16x8 read_row_tr(const uint16_t* p, int lane) {
+  typedef __attribute__((address_space(3))) s16x4* lds;
+  const uint16_t* q = p + (8 * (lane >> 4) + ((lane & 15) >> 2)) * 16 + (lane & 3) * 4;
+  s16x4 v[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)q), __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)(q + 64))};
+  return __builtin_bit_cast(bf16x8, v);
+}
 
 template <int CIS, int COS>
-__global__ __launch_bounds__(256) void wgrad_partial(const uint16_t* __restrict__ xin, const uint16_t* __restrict__ gin,
-                                                     Grid3 g, float* __restrict__ part, int accumulate) {
-  constexpr int P = CIS * COS;                 // weight pairs
-  constexpr int NG = 256 / P;                  // row groups
-  constexpr int ROWS = WTY * WTZ;
-  __shared__ __attribute__((aligned(16))) float xs[CIS][WSZ][WSY][WSX];
-  __shared__ __attribute__((aligned(16))) float gs[COS][ROWS][WTX];
-  __shared__ float red[NG > 1 ? NG : 1][NG > 1 ? P : 1][28];
-  const int tid = threadIdx.x;
-  const int pair = tid % P, rg = tid / P;
-  const int co = pair / CIS, ci = pair % CIS;
+__global__ __launch_bounds__(256, CIS * COS == 256 ? 1 : 2) void wgrad_partial(const uint16_t* __restrict__ xin,
+                                                        const uint16_t* __restrict__ gin, Grid3 g,
+                                                        float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint16_t st[(WXV + WGV) * 16];  // staged X, then G
+  static_assert(sizeof(st) >= WACC * 65 * 4 * sizeof(float), "the wave reduction reuses the stage");
+  uint16_t* xs = st;
+  uint16_t* gs = st + WXV * 16;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: matrix instructions ignore the lane mask
   const int tx = (g.nx + WTX - 1) / WTX, ty = (g.ny + WTY - 1) / WTY, tz = (g.nz + WTZ - 1) / WTZ;
   const int ntiles = tx * ty * tz;
   const int64_t plane = (int64_t)g.nx * g.ny;
-  float acc[27];
-  float accb = 0.f;
+  // index along one axis one past either end: wrapped (periodic) or outside (-1, as anything beyond)
+  auto fold = [&](int i, int n) -> int {
+    if (g.periodic) i = i == -1 ? n - 1 : (i == n ? 0 : i);
+    return i >= 0 && i < n ? i : -1;
+  };
+  f32x4 acc[WACC];
 #pragma unroll
-  for (int t = 0; t < 27; ++t) acc[t] = 0.f;
+  for (int t = 0; t < WACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (CIS < 16 || COS < 16)  // channels the layer does not have stay zero
+    for (int i = tid; i < (WXV + WGV) * 2; i += 256) ((uint4*)st)[i] = make_uint4(0, 0, 0, 0);
 
+  // A thread's load units (16 bytes of a voxel, or a voxel of a narrow layer) are fetched into registers
+  // while the previous tile is multiplied.
+  constexpr int XU = CIS == 16 ? 2 * WXV : WXV, GU = COS == 16 ? 2 * WGV : WGV;
+  constexpr int XN = (XU + 255) / 256, GN = (GU + 255) / 256;
+  using XUnit = typename std::conditional<CIS == 16, uint4, uint32_t>::type;
+  using GUnit = typename std::conditional<COS == 16, uint4, uint16_t>::type;
+  static_assert((CIS == 16 || CIS == 2) && (COS == 16 || COS == 1), "channel counts");
+  XUnit px[XN];
+  GUnit pg[GN];
+  // tiles in turn over the XCDs' own ranges: neighbours that share halo rows meet in one L2
+  auto locate = [&](int tile, int& x0, int& y0, int& z0) {
+    tile = xcd_remap(tile, ntiles);
+    x0 = tile % tx * WTX;
+    y0 = tile / tx % ty * WTY;
+    z0 = tile / (tx * ty) * WTZ;
+  };
+  auto fetch = [&](int tile) {
+    int x0, y0, z0;
+    locate(tile, x0, y0, z0);
+    // X: rows of the grid only (y0 + r < ny, z0 + r < nz)
+#pragma unroll
+    for (int q = 0; q < XN; ++q) {
+      const int u = tid + 256 * q, v = CIS == 16 ? u >> 1 : u;
+      const int gx = fold(x0 - 1 + v % (WTX + 2), g.nx);
+      const int gy = y0 + (v / (WTX + 2)) % WTY, gz = z0 + v / ((WTX + 2) * WTY);
+      px[q] = XUnit{};
+      if (u < XU && gx >= 0 && gy < g.ny && gz < g.nz) {
+        const uint16_t* p = xin + ((int64_t)gz * plane + (int64_t)gy * g.nx + gx) * CIS;
+        px[q] = ((const XUnit*)p)[CIS == 16 ? u & 1 : 0];
+      }
+    }
+    // G: x inside the grid only
+#pragma unroll
+    for (int q = 0; q < GN; ++q) {
+      const int u = tid + 256 * q, v = COS == 16 ? u >> 1 : u;
+      const int gx = x0 + v % WTX;
+      const int gy = fold(y0 - 1 + (v / WTX) % (WTY + 2), g.ny), gz = fold(z0 - 1 + v / (WTX * (WTY + 2)), g.nz);
+      pg[q] = GUnit{};
+      if (u < GU && gx < g.nx && gy >= 0 && gz >= 0) {
+        const uint16_t* p = gin + ((int64_t)gz * plane + (int64_t)gy * g.nx + gx) * COS;
+        pg[q] = ((const GUnit*)p)[COS == 16 ? u & 1 : 0];
+      }
+    }
+  };
+
+  if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int bx = tile % tx, by = (tile / tx) % ty, bz = tile / (tx * ty);
-    const int x0 = bx * WTX, y0 = by * WTY, z0 = bz * WTZ;
-    __syncthreads();
-    for (int v = tid; v < WSX * WSY * WSZ; v += 256) {
-      const int sx = v % WSX, sy = (v / WSX) % WSY, sz = v / (WSX * WSY);
-      int gx = x0 + sx - 2, gy = y0 + sy - 1, gz = z0 + sz - 1;
-      bool ok = true;
-      if (g.periodic) {
-        gx = (gx + g.nx) % g.nx; gy = (gy + g.ny) % g.ny; gz = (gz + g.nz) % g.nz;
-      } else {
-        ok = gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny && gz >= 0 && gz < g.nz;
-      }
-      const int64_t vi = (int64_t)gz * plane + (int64_t)gy * g.nx + gx;
+    int x0, y0, z0;
+    locate(tile, x0, y0, z0);
+    __syncthreads();  // the previous tile's reads (and the zero fill) are done
 #pragma unroll
-      for (int c = 0; c < CIS; ++c) xs[c][sz][sy][sx] = ok ? bf16_to_f32(xin[vi * CIS + c]) : 0.f;
+    for (int q = 0; q < XN; ++q) {
+      const int u = tid + 256 * q;
+      if (XU % 256 == 0 || u < XU) *(XUnit*)(xs + u * (CIS == 16 ? 8 : 16)) = px[q];
     }
-    for (int v = tid; v < ROWS * WTX; v += 256) {
-      const int vx = v % WTX, r = v / WTX;
-      const int gx = x0 + vx, gy = y0 + r % WTY, gz = z0 + r / WTY;
-      const bool ok = gx < g.nx && gy < g.ny && gz < g.nz;  // outputs outside the grid contribute 0
-      const int64_t vi = (int64_t)gz * plane + (int64_t)gy * g.nx + gx;
 #pragma unroll
-      for (int c = 0; c < COS; ++c) gs[c][r][vx] = ok ? bf16_to_f32(gin[vi * COS + c]) : 0.f;
+    for (int q = 0; q < GN; ++q) {
+      const int u = tid + 256 * q;
+      if (GU % 256 == 0 || u < GU) *(GUnit*)(gs + u * (COS == 16 ? 8 : 16)) = pg[q];
     }
+    if (tile + (int)gridDim.x < ntiles) fetch(tile + gridDim.x);
     __syncthreads();
-    for (int r = rg; r < ROWS; r += NG) {
-      const int ry = r % WTY, rz = r / WTY;
-      float gv[WTX];
+    // X row (wave, y), tap (dz, dy, dx): G row (wave + 2 - dz, y + 2 - dy) of the stage
+    bf16x8 a[3][WTY + 2];
 #pragma unroll
-      for (int q = 0; q < WTX; q += 4) {
-        const float4 t4 = *(const float4*)&gs[co][r][q];
-        gv[q] = t4.x; gv[q + 1] = t4.y; gv[q + 2] = t4.z; gv[q + 3] = t4.w;
-      }
-      if (ci == 0) {
+    for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-        for (int q = 0; q < WTX; ++q) accb += gv[q];
-      }
+      for (int r = 0; r < 2; ++r) a[dz][r] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + r) * WTX * 16, lane);
+#pragma unroll
+    for (int y = 0; y < WTY; ++y) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) b[dx] = read_row_tr(xs + ((wave * WTY + y) * (WTX + 2) + dx) * 16, lane);
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+        a[dz][y + 2] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + y + 2) * WTX * 16, lane);
 #pragma unroll
       for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-          float xr[WSX];
-#pragma unroll
-          for (int q = 0; q < WSX; q += 4) {
-            const float4 t4 = *(const float4*)&xs[ci][rz + dz][ry + dy][q];
-            xr[q] = t4.x; xr[q + 1] = t4.y; xr[q + 2] = t4.z; xr[q + 3] = t4.w;
-          }
+        for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
           for (int dx = 0; dx < 3; ++dx) {
-            float s = acc[dz * 9 + dy * 3 + dx];
-#pragma unroll
-            for (int q = 0; q < WTX; ++q) s = __builtin_fmaf(xr[q + dx + 1], gv[q], s);
-            acc[dz * 9 + dy * 3 + dx] = s;
+            const int t = 9 * dz + 3 * dy + dx;
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[dz][y + 2 - dy], b[dx], acc[t], 0, 0, 0);
           }
-        }
+      // biases: the tile's own G rows (dz = dy = 1) times one, times zero for a row beyond the grid
+      const __bf16 one = (__bf16)(y0 + y < g.ny && z0 + wave < g.nz ? 1.0f : 0.0f);
+      const bf16x8 ones = {one, one, one, one, one, one, one, one};
+      acc[27] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][y + 1], ones, acc[27], 0, 0, 0);
     }
   }
-  // combine row groups in a fixed order, then one partial row per block
-  if (NG > 1) {
+  // add the four waves in a fixed order; D layout: acc[t][r] = dW[co = 4 (lane >> 4) + r][ci = lane & 15]
+  float* red = (float*)st;
 #pragma unroll
-    for (int t = 0; t < 27; ++t) red[NG > 1 ? rg : 0][pair][t] = acc[t];
-    red[NG > 1 ? rg : 0][pair][27] = accb;
+  for (int w = 0; w < 4; ++w) {
     __syncthreads();
-    if (rg == 0) {
-      for (int q = 1; q < NG; ++q) {
+    if (wave == w) {
 #pragma unroll
-        for (int t = 0; t < 27; ++t) acc[t] += red[q][pair][t];
-        accb += red[q][pair][27];
+      for (int t = 0; t < WACC; ++t) {
+        f32x4* p = (f32x4*)(red + (t * 65 + lane) * 4);  // 65: taps a bank apart
+        *p = w == 0 ? acc[t] : *p + acc[t];
       }
     }
   }
-  if (rg == 0) {
-    float* row = part + (int64_t)blockIdx.x * WG_PARTS;
-#pragma unroll
-    for (int t = 0; t < 27; ++t) {
-      const int j = (co * CIS + ci) * 27 + t;
-      row[j] = accumulate ? row[j] + acc[t] : acc[t];
-    }
-    if (ci == 0) {
-      const int j = COS * CIS * 27 + co;
-      row[j] = accumulate ? row[j] + accb : accb;
-    }
+  __syncthreads();
+  float* row = part + (int64_t)blockIdx.x * WG_PARTS;
+  for (int j = tid; j < COS * CIS * 27 + COS; j += 256) {
+    const int t = j < COS * CIS * 27 ? j % 27 : 27;
+    const int co = j < COS * CIS * 27 ? j / (27 * CIS) : j - COS * CIS * 27;
+    const int ci = j < COS * CIS * 27 ? (j / 27) % CIS : 0;
+    row[j] = red[(t * 65 + (co >> 2) * 16 + ci) * 4 + (co & 3)];
   }
 }
 
-// grad[woff + j] (+)= sum over partial rows (fixed order, FP64)
-__global__ __launch_bounds__(256) void wgrad_reduce(const float* __restrict__ part, int rows, int count,
-                                                    float* __restrict__ grad, int accumulate) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= count) return;
+// grad[j] (+)= sum over the partial rows, FP64 in a fixed order: a workgroup takes 64 columns, its 16
+// waves every 16th row each: 5.5 us for 256 rows of 6928 columns (268 us for 1024 rows with each column's
+// rows in one thread's chain).
+__global__ __launch_bounds__(1024) void wgrad_reduce(const float* __restrict__ part, int rows, int count,
+                                                     float* __restrict__ grad, int accumulate) {
+  __shared__ double red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + lane;
   double s = 0.0;
-  for (int r = 0; r < rows; ++r) s += part[(int64_t)r * WG_PARTS + j];
-  grad[j] = accumulate ? (float)((double)grad[j] + s) : (float)s;
+  if (j < count) {
+#pragma unroll 4
+    for (int r = wave; r < rows; r += 16) s += part[(int64_t)r * WG_PARTS + j];
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && j < count) {
+#pragma unroll
+    for (int w = 1; w < 16; ++w) s += red[w][lane];
+    grad[j] = accumulate ? (float)((double)grad[j] + s) : (float)s;
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -688,7 +758,10 @@ using namespace tbs::net;
 
 namespace {
 
-constexpr int kPartBlocks = 1024;   // weight-gradient partial rows
+// weight-gradient workgroups (= partial rows), as many as the chip holds at once: two per CU, or one for
+// 16 -> 16 channels, whose prefetch registers fill a SIMD
+constexpr int kPartBlocks = 512;
+constexpr int kPartBlocks16 = 256;
 constexpr int kRedBlocks = 1024;    // blocks of the sum-of-squares / loss reductions
 
 struct NetWs {
@@ -991,29 +1064,29 @@ extern "C" int tbs_net_train_step(tbs_net* n, const float* u, const float* q, co
     const int acc = b > 0;
     // layer 4: dW4 = sum y3 (x) g ; dZ3 = convT(g, W4) * GELU'(z3)
     hipLaunchKernelGGL((wgrad_partial<16, 1>), dim3(wblocks), dim3(256), 0, n->st, (const uint16_t*)w.y[2],
-                       (const uint16_t*)w.gout, g, w.part, 0);
-    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 27 + 1 + 255) / 256), dim3(256), 0, n->st, (const float*)w.part,
+                       (const uint16_t*)w.gout, g, w.part);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 27 + 1 + 63) / 64), dim3(1024), 0, n->st, (const float*)w.part,
                        wblocks, 16 * 27 + 1, w.grad + woff(3), acc);
     hipLaunchKernelGGL((conv_mfma<1, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gout,
                        w.wb + 3 * PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[2], nullptr);
     // layer 3: dW3 = sum y2 (x) dZ3 ; dZ2 = convT(dZ3, W3) * GELU'(z2)
-    hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(wblocks), dim3(256), 0, n->st, (const uint16_t*)w.y[1],
-                       (const uint16_t*)w.gz[0], g, w.part, 0);
-    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 255) / 256), dim3(256), 0, n->st,
-                       (const float*)w.part, wblocks, 16 * 16 * 27 + 16, w.grad + woff(2), acc);
+    hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks16), dim3(256), 0, n->st, (const uint16_t*)w.y[1],
+                       (const uint16_t*)w.gz[0], g, w.part);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 63) / 64), dim3(1024), 0, n->st,
+                       (const float*)w.part, kPartBlocks16, 16 * 16 * 27 + 16, w.grad + woff(2), acc);
     hipLaunchKernelGGL((conv_mfma<16, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gz[0],
                        w.wb + 2 * PACK, nullptr, g, nullptr, w.gz[1], nullptr, (const float*)w.z[1], nullptr);
     // layer 2: dW2 = sum y1 (x) dZ2 ; dZ1 = convT(dZ2, W2) * GELU'(z1)
-    hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(wblocks), dim3(256), 0, n->st, (const uint16_t*)w.y[0],
-                       (const uint16_t*)w.gz[1], g, w.part, 0);
-    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 255) / 256), dim3(256), 0, n->st,
-                       (const float*)w.part, wblocks, 16 * 16 * 27 + 16, w.grad + woff(1), acc);
+    hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks16), dim3(256), 0, n->st, (const uint16_t*)w.y[0],
+                       (const uint16_t*)w.gz[1], g, w.part);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 63) / 64), dim3(1024), 0, n->st,
+                       (const float*)w.part, kPartBlocks16, 16 * 16 * 27 + 16, w.grad + woff(1), acc);
     hipLaunchKernelGGL((conv_mfma<16, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gz[1],
                        w.wb + PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[0], nullptr);
     // layer 1: dW1 = sum x0 (x) dZ1
     hipLaunchKernelGGL((wgrad_partial<2, 16>), dim3(wblocks), dim3(256), 0, n->st, (const uint16_t*)w.x0,
-                       (const uint16_t*)w.gz[0], g, w.part, 0);
-    hipLaunchKernelGGL(wgrad_reduce, dim3((2 * 16 * 27 + 16 + 255) / 256), dim3(256), 0, n->st,
+                       (const uint16_t*)w.gz[0], g, w.part);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((2 * 16 * 27 + 16 + 63) / 64), dim3(1024), 0, n->st,
                        (const float*)w.part, wblocks, 2 * 16 * 27 + 16, w.grad + woff(0), acc);
     NCHK(hipGetLastError());
   }
@@ -1062,12 +1135,12 @@ extern "C" int tbs_net_conv_layer(tbs_net* n, int layer, int mode, const uint16_
   } else {  // weight gradient: out [co][ci][27] then [co] biases
     if (!n->training) return err(TBS_E_STATE, "weight gradients need a training workspace");
     if (!aligned256(x) || !aligned256(gin)) return TBS_E_INVAL;
-    if (ci == 2) hipLaunchKernelGGL((wgrad_partial<2, 16>), dim3(kPartBlocks), dim3(256), 0, n->st, x, gin, g, w.part, 0);
-    else if (co == 16) hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks), dim3(256), 0, n->st, x, gin, g, w.part, 0);
-    else hipLaunchKernelGGL((wgrad_partial<16, 1>), dim3(kPartBlocks), dim3(256), 0, n->st, x, gin, g, w.part, 0);
+    if (ci == 2) hipLaunchKernelGGL((wgrad_partial<2, 16>), dim3(kPartBlocks), dim3(256), 0, n->st, x, gin, g, w.part);
+    else if (co == 16) hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks16), dim3(256), 0, n->st, x, gin, g, w.part);
+    else hipLaunchKernelGGL((wgrad_partial<16, 1>), dim3(kPartBlocks), dim3(256), 0, n->st, x, gin, g, w.part);
     const int cnt = ci * co * 27 + co;
-    hipLaunchKernelGGL(wgrad_reduce, dim3((cnt + 255) / 256), dim3(256), 0, n->st, (const float*)w.part,
-                       kPartBlocks, cnt, out, 0);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((cnt + 63) / 64), dim3(1024), 0, n->st, (const float*)w.part,
+                       ci * co == 256 ? kPartBlocks16 : kPartBlocks, cnt, out, 0);
   }
   NCHK(hipGetLastError());
   return TBS_OK;
