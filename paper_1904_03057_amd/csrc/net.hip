@@ -548,12 +548,23 @@ __global__ __launch_bounds__(256) void sumsq_partial(const T* __restrict__ a, co
   }
 }
 
+// The sums of the reductions' per-block partials below run in one wave: 64 strided chains, then a fixed
+// butterfly (5 us; one thread's chain over the 1024 partials took 92 us for the scales and 58 us for
+// the loss, 13 % of a 256^3 forward pass).
+
 // sc[0] = 1/rms(u), sc[1] = 1/rms(q) (1 where the rms is 0), sc[2] = output scale tau*rms(u)*out_scale
-__global__ void scales_final(const double* __restrict__ part, int blocks, int64_t n, double tau, double out_scale,
-                             double* sc) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(64) void scales_final(const double* __restrict__ part, int blocks, int64_t n, double tau,
+                                                   double out_scale, double* sc) {
   double s0 = 0, s1 = 0;
-  for (int i = 0; i < blocks; ++i) { s0 += part[2 * i]; s1 += part[2 * i + 1]; }
+#pragma unroll 8
+  for (int i = threadIdx.x; i < blocks; i += 64) {
+    const double2 p = ((const double2*)part)[i];
+    s0 += p.x;
+    s1 += p.y;
+  }
+  s0 = wave_sum(s0);
+  s1 = wave_sum(s1);
+  if (threadIdx.x != 0) return;
   const double ru = sqrt(s0 / (double)n), rq = sqrt(s1 / (double)n);
   sc[0] = ru > 0 ? 1.0 / ru : 1.0;
   sc[1] = rq > 0 ? 1.0 / rq : 1.0;
@@ -690,12 +701,13 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restric
     dst[i] = f32_to_bf16(src[i]);
 }
 
-__global__ void loss_final(const double* __restrict__ part, int blocks, double inv_total, double* loss_acc,
-                           int accumulate) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(64) void loss_final(const double* __restrict__ part, int blocks, double inv_total,
+                                                 double* loss_acc, int accumulate) {
   double s = 0;
-  for (int i = 0; i < blocks; ++i) s += part[i];
-  loss_acc[0] = (accumulate ? loss_acc[0] : 0.0) + s * inv_total;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < blocks; i += 64) s += part[i];
+  s = wave_sum(s);
+  if (threadIdx.x == 0) loss_acc[0] = (accumulate ? loss_acc[0] : 0.0) + s * inv_total;
 }
 
 // Adam (Kingma & Ba 2015) on the FP32 master weights; t is the 1-based step
@@ -714,37 +726,39 @@ __global__ __launch_bounds__(256) void adam(float* __restrict__ w, float* __rest
   w[i] = w[i] - lr * mh / (sqrtf(vh) + eps);
 }
 
-// Packed A operands of layer l.  Forward: A[m][k] = W[m][ci][tap] with tap = tap16(s, k >> 4),
-// ci = k & 15 (zero outside the layer's channels and for the padding partners of steps 12-14).  Backward data (flip = 1):
-// the transposed convolution's weights W'[ci][co][tap] = W[co][ci][26 - tap], M = ci, K = (tap, co).
+// Packed A operands of every layer, one wave per (K-step blockIdx.x, layer blockIdx.y, direction
+// blockIdx.z): one launch for the eight that took 25 us each with a wave per layer.  Forward (z = 0):
+// A[m][k] = W[m][ci][tap] with tap = tap16(s, k >> 4), ci = k & 15 (zero outside the layer's channels
+// and for the padding partners of steps 12-14).  Backward data (z = 1): the transposed convolution's
+// weights W'[ci][co][tap] = W[co][ci][26 - tap], M = ci, K = (tap, co).
 // Lane layout of v_mfma_f32_16x16x32_bf16 A: lane holds row (lane & 15), k = 8 (lane >> 4) + j.
-__global__ __launch_bounds__(64) void pack_weights(const float* __restrict__ w, int l, int flip,
-                                                   uint16_t* __restrict__ out, float* __restrict__ bias_out) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64) void pack_weights(const float* __restrict__ w, uint16_t* __restrict__ wf,
+                                                   uint16_t* __restrict__ wb, float* __restrict__ bias) {
+  const int lane = threadIdx.x, s = blockIdx.x, l = blockIdx.y, flip = blockIdx.z;
   const int ci_n = flip ? COUT[l] : CIN[l];   // K-channel count of this convolution
   const int m_n = flip ? CIN[l] : COUT[l];    // output channels
   const float* W = w + woff(l);
+  uint16_t* out = (flip ? wb : wf) + l * PACK;
   const int mrow = lane & 15, grp = lane >> 4;
-  for (int s = 0; s < NSTEP; ++s) {
-    for (int j = 0; j < 8; ++j) {
-      float val = 0.f;
-      if (!flip && ci_n == 2) {
-        // two-channel layout: k = 8 grp + j -> tap 16 s + 4 grp + j/2, channel j % 2 (2 steps)
-        const int tap = 16 * s + 4 * grp + (j >> 1), kc = j & 1;
-        if (s < 2 && tap < 27 && mrow < m_n) val = W[(mrow * CIN[l] + kc) * 27 + tap];
-      } else {
-        const int half = grp >> 1;
-        const int tap = tap16(s, half);
-        const int kc = (grp & 1) * 8 + j;
-        if (!pad16(s, half) && mrow < m_n && kc < ci_n) {
-          if (!flip) val = W[(mrow * CIN[l] + kc) * 27 + tap];
-          else val = W[(kc * CIN[l] + mrow) * 27 + (26 - tap)];
-        }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float val = 0.f;
+    if (!flip && ci_n == 2) {
+      // two-channel layout: k = 8 grp + j -> tap 16 s + 4 grp + j/2, channel j % 2 (2 steps)
+      const int tap = 16 * s + 4 * grp + (j >> 1), kc = j & 1;
+      if (s < 2 && tap < 27 && mrow < m_n) val = W[(mrow * CIN[l] + kc) * 27 + tap];
+    } else {
+      const int half = grp >> 1;
+      const int tap = tap16(s, half);
+      const int kc = (grp & 1) * 8 + j;
+      if (!pad16(s, half) && mrow < m_n && kc < ci_n) {
+        if (!flip) val = W[(mrow * CIN[l] + kc) * 27 + tap];
+        else val = W[(kc * CIN[l] + mrow) * 27 + (26 - tap)];
       }
-      out[(s * 64 + lane) * 8 + j] = f32_to_bf16(val);
     }
+    out[(s * 64 + lane) * 8 + j] = f32_to_bf16(val);
   }
-  if (bias_out && lane < 16) bias_out[lane] = (!flip && lane < COUT[l]) ? w[boff(l) + lane] : 0.f;
+  if (!flip && s == 0 && lane < 16) bias[l * 16 + lane] = lane < COUT[l] ? w[boff(l) + lane] : 0.f;
 }
 
 }  // namespace net
@@ -854,6 +868,13 @@ extern "C" size_t tbs_net_workspace_bytes(const int64_t grid[3], int batch, int 
   return layout(nullptr, nullptr, grid[0] * grid[1] * grid[2], training);
 }
 
+static int repack(tbs_net* n) {
+  hipLaunchKernelGGL(pack_weights, dim3(NSTEP, NL, 2), dim3(64), 0, n->st, (const float*)n->w.master, n->w.wf,
+                     n->w.wb, n->w.bias);
+  NCHK(hipGetLastError());
+  return TBS_OK;
+}
+
 extern "C" int tbs_net_bind_workspace(tbs_net* n, const int64_t grid[3], int batch, int training, void* p,
                                       size_t bytes) {
   if (!n || !grid || batch < 1) return TBS_E_INVAL;
@@ -880,23 +901,12 @@ extern "C" int tbs_net_bind_workspace(tbs_net* n, const int64_t grid[3], int bat
     NCHK(hipMemcpyAsync(n->w.master, host_params, sizeof(host_params), hipMemcpyHostToDevice, n->st));
     NCHK(hipMemcpyAsync(n->w.m, host_m, sizeof(host_m), hipMemcpyHostToDevice, n->st));
     NCHK(hipMemcpyAsync(n->w.v, host_v, sizeof(host_v), hipMemcpyHostToDevice, n->st));
-    for (int l = 0; l < NL; ++l) {
-      hipLaunchKernelGGL(pack_weights, dim3(1), dim3(64), 0, n->st, n->w.master, l, 0, n->w.wf + l * PACK, n->w.bias + l * 16);
-      hipLaunchKernelGGL(pack_weights, dim3(1), dim3(64), 0, n->st, n->w.master, l, 1, n->w.wb + l * PACK, nullptr);
-    }
+    int rc = repack(n);
+    if (rc) return rc;
     NCHK(hipStreamSynchronize(n->st));
   } else {
     n->weights_set = 0;
   }
-  return TBS_OK;
-}
-
-static int repack(tbs_net* n) {
-  for (int l = 0; l < NL; ++l) {
-    hipLaunchKernelGGL(pack_weights, dim3(1), dim3(64), 0, n->st, n->w.master, l, 0, n->w.wf + l * PACK, n->w.bias + l * 16);
-    hipLaunchKernelGGL(pack_weights, dim3(1), dim3(64), 0, n->st, n->w.master, l, 1, n->w.wb + l * PACK, nullptr);
-  }
-  NCHK(hipGetLastError());
   return TBS_OK;
 }
 
