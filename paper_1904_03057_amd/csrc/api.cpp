@@ -154,7 +154,8 @@ struct tbs_ctx {
   RobinCorner rb;    // its corner blocks
   hipStream_t st;
   Taps taps;
-  int tiles_x, tiles_y, nchunks, zc, nblocks, nparts;
+  int zc[M_RHSRES + 1][2];  // planes per z-chunk of each stencil mode, in FP32 and FP64
+  int nparts;               // partial sums of the largest launch
   char* ws;
   size_t ws_bytes;
   tbs_opts opts;
@@ -184,24 +185,18 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 static bool aligned_ptr(const void* p) { return p && ((uintptr_t)p & 255u) == 0; }
 
+static StencilArgs base_args(const tbs_ctx* c, int mode, int compute_bytes);
+
 static void plan_geometry(tbs_ctx* c, int zchunk) {
-  c->tiles_x = (int)((c->nx + kTileX - 1) / kTileX);
-  c->tiles_y = (int)((c->ny + kTileY - 1) / kTileY);  // finest tiling: bounds the partial-sum count
-  const int64_t tiles = (int64_t)c->tiles_x * c->tiles_y;
-  const int64_t plan_tiles = (int64_t)c->tiles_x * ((c->ny + kTileYPlan - 1) / kTileYPlan);
-  // about 8192 workgroups (many times what 256 CUs hold at once: the z-marching waves finish at
-  // different times and short chunks even out the tail), but chunks of at least 4(2n+1) planes;
-  // at 928^3 this gives 93-plane chunks, 1 % faster for the CG iteration than 186
-  int64_t want = (8192 + plan_tiles - 1) / plan_tiles;
-  const int64_t minzc = std::max<int64_t>(16, 4 * (2 * c->n + 1));
-  int64_t maxchunks = std::max<int64_t>(1, c->nz / minzc);
-  int64_t chunks = std::min(want, maxchunks);
-  if (chunks < 1) chunks = 1;
-  c->zc = (int)((c->nz + chunks - 1) / chunks);
-  if (zchunk > 0) c->zc = (int)std::min<int64_t>(zchunk, c->nz);
-  c->nchunks = (int)((c->nz + c->zc - 1) / c->zc);
-  c->nblocks = (int)(tiles * c->nchunks);
-  c->nparts = std::max(c->nblocks, kVecBlocks);
+  c->nparts = kVecBlocks;
+  for (int mode = M_APPLY; mode <= M_RHSRES; ++mode)
+    for (int f64 = 0; f64 < 2; ++f64) {
+      const int es = f64 ? 8 : 4;
+      // RHSRES stands in for RESID: the same launch shape, so that its partial sums do too
+      c->zc[mode][f64] = stencil_plan_zc(c->nx, c->ny, c->nz, mode == M_RHSRES ? M_RESID : mode, es, c->n, c->bc, zchunk);
+      if (mode == M_CG1 || mode == M_CGF || (f64 && (mode == M_RESID || mode == M_RHSRES)))
+        c->nparts = std::max(c->nparts, stencil_blocks(base_args(c, mode, es), mode, es, c->n, c->bc));
+    }
 }
 
 // workspace layout: [scalars x4][part0][part1][part2][part3][arrays...]
@@ -248,11 +243,13 @@ static double* part1(const tbs_ctx* c) { return (double*)(c->ws + 1024 + align25
 static double* part2(const tbs_ctx* c) { return (double*)(c->ws + 1024 + 2 * align256((size_t)c->nparts * 8)); }
 static double* part3(const tbs_ctx* c) { return (double*)(c->ws + 1024 + 3 * align256((size_t)c->nparts * 8)); }
 
-static StencilArgs base_args(const tbs_ctx* c) {
+// mode, compute_bytes: of the launch the arguments are for (its z-chunks)
+static StencilArgs base_args(const tbs_ctx* c, int mode, int compute_bytes) {
   StencilArgs a{};
   a.rscale = 1.0;
-  a.nx = (int)c->nx; a.ny = (int)c->ny; a.nz = (int)c->nz; a.zc = c->zc;
-  a.tiles_x = c->tiles_x; a.tiles_y = c->tiles_y; a.nchunks = c->nchunks; a.nblocks = c->nblocks;
+  a.nx = (int)c->nx; a.ny = (int)c->ny; a.nz = (int)c->nz;
+  a.zc = c->zc[mode][compute_bytes == 8];
+  a.nchunks = (int)((c->nz + a.zc - 1) / a.zc);
   a.t = c->taps;
   if (c->ws) {
     a.part0 = part0(c);
@@ -331,6 +328,7 @@ extern "C" int tbs_setup_robin(tbs_ctx** out, const int64_t grid[3], int degree,
   c->bc = TBS_BC_ROBIN;
   c->gamma = gamma;
   robin_corners(degree, h, tau, gamma, &c->rb);
+  plan_geometry(c, 0);  // the Robin kernels' tiles
   return TBS_OK;
 }
 
@@ -535,7 +533,7 @@ extern "C" int tbs_apply(tbs_ctx* c, const void* u, int in_dt, void* y, int out_
                   (in_dt == TBS_BF16 && out_dt == TBS_F32) || (in_dt == TBS_F32 && out_dt == TBS_F64) ||
                   (in_dt == TBS_BF16 && out_dt == TBS_F64);
   if (!ok) return set_err(TBS_E_INVAL, "unsupported dtype combination (%d -> %d)", in_dt, out_dt);
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_APPLY, out_dt == TBS_F64 ? 8 : 4);
   a.in0 = u;
   a.out0 = y;
   const double esz[3] = {8, 4, 2};
@@ -553,7 +551,7 @@ extern "C" int tbs_rhs(tbs_ctx* c, const void* u_prev, const void* q, void* b, i
     return set_err(TBS_E_INVAL, "arrays must be 256-byte aligned device pointers");
   if (b == u_prev || b == q) return set_err(TBS_E_INVAL, "b must not alias the inputs");
   if (dt != TBS_F64 && dt != TBS_F32) return set_err(TBS_E_INVAL, "rhs dtype must be F64 or F32");
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_RHS, dt == TBS_F64 ? 8 : 4);
   a.in0 = u_prev;
   a.in1 = q;
   a.out0 = b;
@@ -609,7 +607,7 @@ extern "C" int tbs_apply_varcoef(tbs_ctx* c, const void* u, const void* d, const
 
 // b = M u (FP64) and r = b - A u (FP32) in one pass (source-free step, no Robin), norms to scal slot
 static int rhs_resid_async(tbs_ctx* c, const double* u, double* b, void* r, int slot) {
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_RHSRES, 8);
   a.in0 = u;
   a.out1 = b;
   a.out0 = r;
@@ -624,7 +622,7 @@ static int rhs_resid_async(tbs_ctx* c, const double* u, double* b, void* r, int 
 // r = (b - A x) rscale (FP64), its norms to scal slot; r written if r != NULL (r_dt F64/F32)
 static int resid_async(tbs_ctx* c, const double* x, const double* b, void* r, int r_dt, int slot, int fin_op,
                        double rtol, double rscale = 1.0) {
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_RESID, 8);
   a.rscale = rscale;
   a.in0 = x;
   a.bvec = b;
@@ -695,7 +693,7 @@ extern "C" int tbs_residual_noalloc(tbs_ctx* c, const double* x, const double* b
   if ((void*)norms == (void*)x || (void*)norms == (void*)b || (r && (void*)norms == r))
     return set_err(TBS_E_INVAL, "norms must not alias the arrays");
   if (r && r_dt != TBS_F64 && r_dt != TBS_F32) return set_err(TBS_E_INVAL, "r dtype must be F64 or F32");
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_RESID, 8);
   const int nb = stencil_blocks(a, M_RESID, 8, c->n, c->bc);
   if (nb > kNoAllocMaxBlocks)
     return set_err(TBS_E_INVAL, "residual launch needs %d workgroups, the static buffer holds %d", nb, kNoAllocMaxBlocks);
@@ -770,7 +768,7 @@ struct CgArrays {
 };
 
 static int cg1_async(tbs_ctx* c, const CgArrays& A, int dt, int k) {
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_CG1, dt == 0 ? 8 : 4);
   a.in0 = A.r;
   a.in1 = A.p[k & 1];
   a.out1 = A.p[(k + 1) & 1];
@@ -799,7 +797,7 @@ static int cg1_async(tbs_ctx* c, const CgArrays& A, int dt, int k) {
 // updates).  r, p and q alternate between two arrays (halo reads of the old values and writes of
 // the new ones overlap in one launch).
 static int cgf_async(tbs_ctx* c, const CgArrays& A, int dt, int k) {
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_CGF, dt == 0 ? 8 : 4);
   void* R[2] = {A.r, A.r2};
   void* Q[2] = {A.q, A.q2};
   a.in0 = R[k & 1];
@@ -878,7 +876,7 @@ static int cg_loop(tbs_ctx* c, const CgArrays& A, int dt, int k0, int max_iter, 
 static int cg_init_async(tbs_ctx* c, const void* b, const CgArrays& A, int dt, double rtol) {
   if (dt == 0) return resid_async(c, (const double*)A.x, (const double*)b, A.r, TBS_F64, SC_CG, FIN_INIT, rtol);
   // FP32: q = A x, then r = b - q with the partial sums of r.r and b.b
-  StencilArgs a = base_args(c);
+  StencilArgs a = base_args(c, M_APPLY, 4);
   a.in0 = A.x;
   a.out0 = A.q;
   HIPCHK(launch_apply(a, c->n, c->bc, 1, 1, c->st));
@@ -1104,7 +1102,7 @@ extern "C" int tbs_timestep(tbs_ctx* c, const double* u_prev, const double* q, d
       float* adu = (float*)(c->ws + L.off[refined ? 5 : 4]);
       rc = resid_async(c, u_prev, b64, r0, TBS_F32, SC_AUX, FIN_NORMS, 0.0);
       if (rc) return rc;
-      StencilArgs a = base_args(c);
+      StencilArgs a = base_args(c, M_APPLY, 4);
       a.in0 = du;
       a.out0 = adu;
       HIPCHK(launch_apply(a, c->n, c->bc, 1, 1, c->st));
@@ -1336,7 +1334,7 @@ extern "C" int tbs_timestep(tbs_ctx* c, const double* u_prev, const double* q, d
       const bool dzero = c->opts.fused_cg != 0;
       if (!dzero) HIPCHK(launch_fill(d32, 1, c->N, c->st));
       HIPCHK(launch_finalize(dzero ? FIN_INIT_XZERO : FIN_INIT, part0(c), part0(c),
-                             stencil_blocks(base_args(c), M_RESID, 8, c->n, c->bc), scal(c, SC_CG), eta, c->st));
+                             stencil_blocks(base_args(c, M_RESID, 8), M_RESID, 8, c->n, c->bc), scal(c, SC_CG), eta, c->st));
       c->cgf_xzero = dzero;
       int nit = 0;
       const int cap = std::min(c->opts.inner_max_iter, std::max(1, max_iter - total));

@@ -32,10 +32,6 @@ namespace tbs {
 
 constexpr int kTileX = 64;
 constexpr int imin(int a, int b) { return a < b ? a : b; }
-// smallest tile height of any stencil launch (the one-kernel CG iteration takes 16 rows or more in
-// FP32, 8 or 16 in FP64): sizes the partial-sum buffers
-constexpr int kTileY = imin(imin(STENCIL_RESID_TY, STENCIL_TY), imin(STENCIL_CG_TY, 8));
-constexpr int kTileYPlan = 16;  // tile height the z-chunk plan assumes
 constexpr int kLdsMax = 160 * 1024;  // LDS one workgroup may hold on gfx950
 
 // Rows per row wave of the one-kernel CG iteration: four in FP32, two in FP64.
@@ -78,6 +74,29 @@ constexpr int stencil_tile_wy(int mode, int compute_bytes, int n, int bc) {
                        : ((mode == M_RESID || mode == M_RHSRES) ? STENCIL_RESID_WY
                                                                    : (compute_bytes == 8 ? STENCIL_F64_WY : 4));
 }
+// Planes per z-chunk of a launch.  A workgroup marches zc + 2n planes; with W workgroups the busiest
+// of the 256 CUs gets ceil(W / 256) of them, and a CU's time per plane grows with that number from
+// the value at which it is busy (below it, the plane's latency counts).  The plan takes the chunk
+// count with the smallest (zc + 2n) max(latency load, ceil(W / 256)): one chunk per plane on the
+// smallest grids, all CUs evenly loaded on the middle ones, long chunks on the largest.  Above four
+// workgroups per CU they no longer start and end together: W / 256 plus a share for the uneven end
+// replaces the ceiling (which took four chunks for the FP32 apply at 928^3: 1.81 against 1.72 ms); 0.75,
+// or 1.5 for the FP32 apply, which is bound by its arithmetic and not by the halo planes' traffic (with
+// 1.5 for all, twelve chunks instead of eight, the FP32 CG step at 928^3 took 292 against 280 ms).
+// FP64 CG on a Robin box of degree 2 or more keeps chunks of at least 4 (2n+1) planes: its nearly empty
+// corner functions take hundreds to thousands of iterations, and sums grouped in another way moved
+// its solutions by up to 4e-8 of their RMS.  The latency
+// loads are the measured ratios of a lone workgroup's time per plane to the added time of one more
+// on the same CU.  Measured (cubic, us per launch, against chunks of at least 4 (2n+1) planes and
+// about 8192 workgroups for every kernel): FP64 CG iteration 67 -> 18 at 32^3, 78 -> 36 at 128^3, 262 ->
+// 198 at 256^3; FP32 CG iteration 93 -> 24 at 64^3, 102 -> 55 at 192^3; FP32 apply 75 -> 20 at 100^3, 79 ->
+// 52 at 256^3; the model's ratios hold within 5 % up to 400^3.
+constexpr double stencil_latency_load(int mode, int compute_bytes) {
+  return mode == M_CGF ? 1.0 : (compute_bytes == 4 ? 1.8 : ((mode == M_RESID || mode == M_RHSRES) ? 1.5 : 1.3));
+}
+// zchunk > 0: the caller's own chunk length
+int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk);
+
 // One stencil launch of degree N for a (mode, input, compute, output) type combination and
 // boundary condition BC; defined in stencil_kernel.h and instantiated per degree and boundary
 // condition by stencil_inst.hip.

@@ -1,5 +1,8 @@
 // Dispatch of the stencil launches: (mode, dtype) combinations, basis degree n and boundary -> the
 // kernel instances of stencil_kernel.h that stencil_inst.hip compiles per degree and boundary.
+#include <algorithm>
+#include <cmath>
+
 #include "common.h"
 #include "stencil.h"
 
@@ -24,6 +27,32 @@ int stencil_blocks(const StencilArgs& a, int mode, int compute_bytes, int n, int
   const int ty = stencil_tile_y(mode, compute_bytes, n, bc);
   const int wx = (mode == M_APPLY && compute_bytes == 4) ? STENCIL_APPLY_WX : 1;
   return ((a.nx + 64 * wx - 1) / (64 * wx)) * ((a.ny + ty - 1) / ty) * a.nchunks;
+}
+
+int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk) {
+  if (zchunk > 0) return (int)std::min<int64_t>(zchunk, nz);
+  const int ty = stencil_tile_y(mode, compute_bytes, n, bc);
+  const int wx = (mode == M_APPLY && compute_bytes == 4) ? STENCIL_APPLY_WX : 1;
+  const int64_t tiles = ((nx + 64 * wx - 1) / (64 * wx)) * ((ny + ty - 1) / ty);
+  if (compute_bytes == 8 && (mode == M_CGF || mode == M_CG1) && bc == BC_ROBIN && n >= 2) {
+    const int64_t plan_tiles = ((nx + 63) / 64) * ((ny + 15) / 16);
+    const int64_t chunks = std::max<int64_t>(1, std::min((8192 + plan_tiles - 1) / plan_tiles, nz / (4 * (2 * n + 1))));
+    return (int)((nz + chunks - 1) / chunks);
+  }
+  const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(1, 16384 / tiles));
+  const double lat = stencil_latency_load(mode, compute_bytes), tail = mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75;
+  int64_t best = nz;
+  double cost = 0.0;
+  for (int64_t want = 1; want <= most; ++want) {
+    const int64_t zc = (nz + want - 1) / want, chunks = (nz + zc - 1) / zc;
+    const double per_cu = (double)(tiles * chunks) / 256.0;
+    const double t = (double)(zc + 2 * n) * std::max(lat, per_cu <= 4.0 ? std::ceil(per_cu) : per_cu + tail);
+    if (want == 1 || t < cost) {
+      cost = t;
+      best = zc;
+    }
+  }
+  return (int)best;
 }
 
 // dtype codes: 0 = f64, 1 = f32, 2 = bf16

@@ -565,7 +565,7 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(BC
 // host-side launch helpers
 
 // Tile shape per (degree, mode, compute type, boundary): heights and row waves from stencil.h (the
-// host sizes the partial-sum buffers for the smallest height); the FP32 apply may take WX column
+// host sizes the partial-sum buffers by stencil_blocks); the FP32 apply may take WX column
 // groups (STENCIL_APPLY_WX, one by default).
 template <int N, int MODE, typename Tc, int BC> constexpr int tile_y() {
   return stencil_tile_y(MODE, (int)sizeof(Tc), N, BC);
@@ -584,7 +584,6 @@ hipError_t launch_bcx(const StencilArgs& a0, bool vec, hipStream_t st) {
   constexpr int TY = tile_y<N, MODE, Tc, BC>();
   constexpr int WX = tile_wx<MODE, Tc>();
   constexpr int WY = tile_wy<N, MODE, Tc, BC>();
-  static_assert(TY >= kTileY, "the partial-sum buffers hold one sum per tile of kTileY rows");
   StencilArgs a = a0;  // geometry for this tile shape
   a.tiles_x = (a.nx + 64 * WX - 1) / (64 * WX);
   a.tiles_y = (a.ny + TY - 1) / TY;
