@@ -74,6 +74,22 @@ constexpr int stencil_tile_wy(int mode, int compute_bytes, int n, int bc) {
                        : ((mode == M_RESID || mode == M_RHSRES) ? STENCIL_RESID_WY
                                                                    : (compute_bytes == 8 ? STENCIL_F64_WY : 4));
 }
+// Columns per lane of the x-pass.  Two: the LDS reads of a row drop from 2N + 1 values per output to
+// N + 1 or N + 2 per two outputs (in pairs), which is what bounds the FP64 kernels of high degree and
+// saves instruction slots in FP32: measured FP64 apply, quartic 385x259x201, 152 against 178 us, FP32 apply
+// cubic 928^3 1.88 against 1.95 ms, FP64 CG iteration quadratic 400^3 762 against 833 us.  One where
+// the pairs read no less (linear) or the copy rate already bounds the launch (FP64 quadratic apply 308
+// against 294 us, residual 425 against 405 us at 400^3).
+constexpr int stencil_x_cols(int mode, int compute_bytes, int n) {
+  return n >= 3 || compute_bytes == 4 || (n == 2 && (mode == M_CG1 || mode == M_CGF)) ? 2 : 1;
+}
+// Waves per SIMD the register allocation must leave room for.  Robin kernels: two.  The linear FP64
+// kernels of eight waves: six, three workgroups per CU; they need 74 to 82 registers and six waves
+// have 80 (residual at 400^3: 280 against 394 us at 82 registers; right-hand side 214 against 274 us at 81).
+constexpr int stencil_min_waves(int mode, int compute_bytes, int n, int bc) {
+  return bc == BC_ROBIN ? 2 : (n == 1 && compute_bytes == 8 && (mode == M_APPLY || mode == M_RHS || mode == M_RESID) ? 6 : 1);
+}
+
 // Planes per z-chunk of a launch.  A workgroup marches zc + 2n planes; with W workgroups the busiest
 // of the 256 CUs gets ceil(W / 256) of them, and a CU's time per plane grows with that number from
 // the value at which it is busy (below it, the plane's latency counts).  The plan takes the chunk

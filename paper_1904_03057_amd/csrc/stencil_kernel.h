@@ -40,13 +40,16 @@ template <typename Ts, typename Tc> __device__ __forceinline__ Ts from_c(Tc v) {
 template <> __device__ __forceinline__ uint16_t from_c<uint16_t, float>(float v) { return f32_to_bf16(v); }
 
 template <int N, int TY, int MODE, typename Tin, typename Tc, typename Tout, int BC, bool VEC, int WX, int WY>
-__global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(BC == BC_ROBIN ? 2 : 1))) void stencil_kernel(StencilArgs a) {
+__global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(stencil_min_waves(MODE, (int)sizeof(Tc), N, BC)))) void stencil_kernel(StencilArgs a) {
   constexpr int NT = 64 * WX * WY;                 // threads: WX column groups of 64 x WY row waves
   constexpr int VE = VEC ? 16 / (int)sizeof(Tin) : 1;
   using Raw = VecN<Tin, VE>;   // staged input (u, u_prev, x, p_old)
   using RawC = VecN<Tc, VE>;   // companion compute-precision vectors (q of RHS; r and x of CG1)
   constexpr int TX = 64 * WX;
-  constexpr int HX = ((N + VE - 1) / VE) * VE;   // x-halo rounded to whole vectors
+  constexpr bool CG = (MODE == M_CG1 || MODE == M_CGF);
+  constexpr int XC = stencil_x_cols(MODE, (int)sizeof(Tc), N);  // columns per lane of the x-pass
+  // x-halo rounded to whole vectors, and to the columns of the x-pass
+  constexpr int HX = ((N + (VE > XC ? VE : XC) - 1) / (VE > XC ? VE : XC)) * (VE > XC ? VE : XC);
   constexpr int R = TY + 2 * N;                   // staged rows
   constexpr int C = TX + 2 * HX;                  // staged columns
   constexpr int CV = C / VE;                      // vectors per staged row
@@ -57,7 +60,6 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(BC
   constexpr int NVH = (HALO + NT - 1) / NT;        // halo vectors per thread
   constexpr int NV = NVC + NVH;
   constexpr int RPW = TY / WY;                     // output rows per wave
-  constexpr bool CG = (MODE == M_CG1 || MODE == M_CGF);
   constexpr bool RR = (MODE == M_RHSRES);  // b = M u and r = b - A u in one pass (no Robin corners)
   constexpr bool RES = (MODE == M_RESID || RR);
   static_assert(!(RR && BC == BC_ROBIN), "the fused rhs and residual has no Robin corner terms");
@@ -65,9 +67,9 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(BC
   constexpr int QD = CG ? N + 1 : 1;  // depth of the centre-value rings (CG1, CGF)
   static_assert(TY % WY == 0, "TY must be a multiple of the row waves");
 
-  __shared__ Tc stage[R * C];
-  __shared__ Tc su[R * TX];
-  __shared__ Tc sv[R * TX];
+  __shared__ __attribute__((aligned(16))) Tc stage[R * C];
+  __shared__ __attribute__((aligned(16))) Tc su[R * TX];
+  __shared__ __attribute__((aligned(16))) Tc sv[R * TX];
   __shared__ Tc cring[QD * TY * TX];  // p at the own points of the last n+1 planes (p.q)
   // CGF: r at the own points of the last n+2 planes (r.q).  It is written while a plane is staged,
   // before the barrier that follows, so it keeps one plane more than cring: the slot being written
@@ -359,42 +361,63 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(BC
           for (int i = 0; i < RPW; ++i)
             cring[(qs * TY + wave * RPW + i) * TX + col] = stage[(wave * RPW + i + N) * C + col + HX];
         }
-        // x-pass over all R staged rows (rows dealt to the waves round-robin)
-#pragma unroll 2
-        for (int r = wave; r < R; r += WY) {
-          const Tc* row = stage + r * C + HX + col;
-          const Tc c0 = row[0];
-          Tc U = m[0] * c0;
-          Tc Vv = mx[0] * c0;
+        // x-pass over all R staged rows (groups of XC rows dealt to the waves round-robin), XC adjacent
+        // columns per lane: with two, a lane reads one window of aligned pairs, N + 1 or N + 2 of them
+        // for both outputs instead of 2N + 1 values for each
+        constexpr int HP = XC == 2 ? ((N + 1) / 2) * 2 : N;  // window start: N columns to the left, at a pair
+        constexpr int XU = XC == 2 ? 1 : 2;  // unrolling of the row loop
+        using Cols = VecN<Tc, XC>;
+        const int cx = (wv % WX) * 64 + XC * (lane % (64 / XC));
+#pragma unroll XU
+        for (int rg = wave; rg < (R + XC - 1) / XC; rg += WY) {
+          const int r = XC * rg + lane / (64 / XC);
+          if (R % XC != 0 && r >= R) continue;
+          const Tc* row = stage + r * C + HX + cx;
+          Tc w[2 * HP + XC];
 #pragma unroll
-          for (int j = 1; j <= N; ++j) {
-            const Tc sm = row[-j] + row[j];
-            U = fmad(m[j], sm, U);
-            Vv = fmad(mx[j], sm, Vv);
+          for (int j = 0; j < 2 * HP + XC; j += XC) {
+            const Cols v = *(const Cols*)(row - HP + j);
+#pragma unroll
+            for (int e = 0; e < XC; ++e) w[j + e] = v.x[e];
           }
-          if constexpr (BC == BC_ROBIN) {
-            // corner blocks of Mx and Mx + Wx: output column gx in the first / last z columns
-            constexpr int zr = 2 * (N / 2) + 1;
-            const int gx = x0 + col;
-            if (gx < zr) {
+          Cols Uo, Vo;
 #pragma unroll
-              for (int cc = 0; cc < zr; ++cc) {
-                const Tc v = row[cc - gx];
-                U = fmad(rbt[gx * kRobinMaxZ + cc], v, U);
-                Vv = fmad(rbt[RBT + gx * kRobinMaxZ + cc], v, Vv);
-              }
-            } else if (gx >= nx - zr && gx < nx) {
-              const int rr = nx - 1 - gx;
+          for (int e = 0; e < XC; ++e) {
+            const Tc c0 = w[HP + e];
+            Tc U = m[0] * c0;
+            Tc Vv = mx[0] * c0;
 #pragma unroll
-              for (int cc = 0; cc < zr; ++cc) {
-                const Tc v = row[rr - cc];
-                U = fmad(rbt[rr * kRobinMaxZ + cc], v, U);
-                Vv = fmad(rbt[RBT + rr * kRobinMaxZ + cc], v, Vv);
+            for (int j = 1; j <= N; ++j) {
+              const Tc sm = w[HP + e - j] + w[HP + e + j];
+              U = fmad(m[j], sm, U);
+              Vv = fmad(mx[j], sm, Vv);
+            }
+            if constexpr (BC == BC_ROBIN) {
+              // corner blocks of Mx and Mx + Wx: output column gx in the first / last z columns
+              constexpr int zr = 2 * (N / 2) + 1;
+              const int gx = x0 + cx + e;
+              if (gx < zr) {
+#pragma unroll
+                for (int cc = 0; cc < zr; ++cc) {
+                  const Tc v = row[e + cc - gx];
+                  U = fmad(rbt[gx * kRobinMaxZ + cc], v, U);
+                  Vv = fmad(rbt[RBT + gx * kRobinMaxZ + cc], v, Vv);
+                }
+              } else if (gx >= nx - zr && gx < nx) {
+                const int rr = nx - 1 - gx;
+#pragma unroll
+                for (int cc = 0; cc < zr; ++cc) {
+                  const Tc v = row[e + rr - cc];
+                  U = fmad(rbt[rr * kRobinMaxZ + cc], v, U);
+                  Vv = fmad(rbt[RBT + rr * kRobinMaxZ + cc], v, Vv);
+                }
               }
             }
+            Uo.x[e] = U;
+            Vo.x[e] = Vv;
           }
-          su[r * TX + col] = U;
-          sv[r * TX + col] = Vv;
+          *(Cols*)(su + r * TX + cx) = Uo;
+          *(Cols*)(sv + r * TX + cx) = Vo;
         }
       }
       __syncthreads();
