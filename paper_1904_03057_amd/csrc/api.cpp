@@ -576,11 +576,9 @@ extern "C" int tbs_apply_varcoef(tbs_ctx* c, const void* u, const void* d, const
   VarcoefArgs a{};
   a.nx = (int)c->nx; a.ny = (int)c->ny; a.nz = (int)c->nz;
   a.tiles_x = (int)((c->nx + vc_tile_x(n) - 1) / vc_tile_x(n));
-  a.tiles_y = (int)((c->ny + kVcTileY - 1) / kVcTileY);
-  // about 16384 single-wave workgroups, z-chunks of at least 16 planes
-  const int64_t strips = (int64_t)a.tiles_x * a.tiles_y;
-  int64_t chunks = std::min<int64_t>((16384 + strips - 1) / strips, std::max<int64_t>(1, c->nz / 16));
-  a.zc = (int)((c->nz + chunks - 1) / chunks);
+  const int tile_y = vc_tile_y(dt == TBS_F64 ? 0 : 1);
+  a.tiles_y = (int)((c->ny + tile_y - 1) / tile_y);
+  a.zc = plan_zc((int64_t)a.tiles_x * a.tiles_y, c->nz, n, 256, 16384, kVcLatencyLoad, 0.75);
   a.nchunks = (int)((c->nz + a.zc - 1) / a.zc);
   a.nblocks = a.tiles_x * a.tiles_y * a.nchunks;
   a.c = u; a.d = d; a.m = m; a.y = y;

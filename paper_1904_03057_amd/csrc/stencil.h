@@ -110,6 +110,7 @@ constexpr int stencil_min_waves(int mode, int compute_bytes, int n, int bc) {
 constexpr double stencil_latency_load(int mode, int compute_bytes) {
   return mode == M_CGF ? 1.0 : (compute_bytes == 4 ? 1.8 : ((mode == M_RESID || mode == M_RHSRES) ? 1.5 : 1.3));
 }
+int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail);
 // zchunk > 0: the caller's own chunk length
 int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk);
 

@@ -29,6 +29,24 @@ int stencil_blocks(const StencilArgs& a, int mode, int compute_bytes, int n, int
   return ((a.nx + 64 * wx - 1) / (64 * wx)) * ((a.ny + ty - 1) / ty) * a.nchunks;
 }
 
+// The planes per chunk with the smallest (zc + halo) max(lat, load), load the workgroups of the busiest of
+// `slots` equal processors; at most most_blocks workgroups, or one chunk.
+int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail) {
+  const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(1, most_blocks / tiles));
+  int64_t best = nz;
+  double cost = 0.0;
+  for (int64_t want = 1; want <= most; ++want) {
+    const int64_t zc = (nz + want - 1) / want, chunks = (nz + zc - 1) / zc;
+    const double load = (double)(tiles * chunks) / slots;
+    const double t = (double)(zc + halo) * std::max(lat, load <= 4.0 ? std::ceil(load) : load + tail);
+    if (want == 1 || t < cost) {
+      cost = t;
+      best = zc;
+    }
+  }
+  return (int)best;
+}
+
 int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk) {
   if (zchunk > 0) return (int)std::min<int64_t>(zchunk, nz);
   const int ty = stencil_tile_y(mode, compute_bytes, n, bc);
@@ -39,20 +57,8 @@ int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_by
     const int64_t chunks = std::max<int64_t>(1, std::min((8192 + plan_tiles - 1) / plan_tiles, nz / (4 * (2 * n + 1))));
     return (int)((nz + chunks - 1) / chunks);
   }
-  const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(1, 16384 / tiles));
-  const double lat = stencil_latency_load(mode, compute_bytes), tail = mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75;
-  int64_t best = nz;
-  double cost = 0.0;
-  for (int64_t want = 1; want <= most; ++want) {
-    const int64_t zc = (nz + want - 1) / want, chunks = (nz + zc - 1) / zc;
-    const double per_cu = (double)(tiles * chunks) / 256.0;
-    const double t = (double)(zc + 2 * n) * std::max(lat, per_cu <= 4.0 ? std::ceil(per_cu) : per_cu + tail);
-    if (want == 1 || t < cost) {
-      cost = t;
-      best = zc;
-    }
-  }
-  return (int)best;
+  return plan_zc(tiles, nz, 2 * n, 256, 16384, stencil_latency_load(mode, compute_bytes),
+                 mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75);
 }
 
 // dtype codes: 0 = f64, 1 = f32, 2 = bf16

@@ -13,16 +13,27 @@
 // coefficient) this is about 6.7 k multiply-adds for cubic splines, against the (2n+1)^3 products
 // of three-index kernels per output.
 //
-// Execution: one wave owns a strip of 64 coefficient columns (64 - 2n output columns and an
-// n-column halo on each side) and kVcTileY output rows, and marches through a z-chunk cell by
-// cell.  For each z-cell and z-point it marches along y: a ring of n+1 rows of the z-interpolated
-// fields (per lane: its column), the y-interpolation, the x-interpolation from the n neighbouring
-// lanes (cross-lane shuffles), the point products, the x-projection (partial sums handed back to
-// the output lanes by shuffles), the y-projection into a ring of n+1 output rows, and finally the
-// z-projection into an LDS accumulator of n+1 output planes x kVcTileY rows per lane.  A plane is
-// written to memory once the z-march has passed it.  Every output sums its terms in one fixed
-// order: results are independent of the launch geometry's z-chunking only up to rounding of the
-// (identical) per-cell terms, and bitwise reproducible for a given geometry.
+// Execution: a workgroup owns a strip of 64 coefficient columns (64 - 2n output columns and an
+// n-column halo on each side) and vc_tile_y output rows, and marches through a z-chunk cell by cell.
+// Its waves take the (z-cell, z-point) pairs in turn.  For its z-point a wave marches along y: a ring of
+// n+1 rows of the z-interpolated fields (per lane: its column), the y-interpolation, the
+// x-interpolation from the n neighbouring lanes (cross-lane shuffles), the point products, the
+// x-projection (partial sums handed back to the output lanes by shuffles), and the y-projection into a
+// ring of n+1 output rows that it leaves in LDS.  The waves then project the finished z-points, in
+// order, onto an LDS accumulator of n+1 output planes (each wave its own rows); a plane is written to
+// memory once the z-march has passed it.  Every output sums its terms in one fixed order, so results
+// are bitwise reproducible and do not depend on the z-chunks.
+//
+// What bounds it is the vector ALU (225 instructions per 64 columns, row, y- and z-point for cubic FP32)
+// and the halo cells.  The x-axis works on the even and odd parts of the basis under the cell's
+// mirror symmetry and takes both points of a mirrored pair from one evaluation (104 + 68 multiply-adds
+// and additions per point row instead of 120 + 80), and the point weights and h_d^-2 are folded into
+// the projection tables (4 multiplications per point instead of 10).  Splitting a cell's z-points over the
+// waves gives four times the waves without more halo cells, and the wave-uniform z-point keeps the
+// tables in scalar registers (cubic: 109 vector registers in FP32 and 156 in FP64; 191 and 314 in the
+// form it replaces, which gave each wave its own strip of all z-points).  Measured, against that form:
+// cubic 192^3 FP32 2.39 against 6.74 ms, FP64 3.87 against 8.38; 400^3 FP32 14.8 against 24.9, FP64 28.6
+// against 42.5; quartic 128^3 FP32 3.7 against 21.8; quintic 100^3 FP32 5.1 against 42.1.
 #include "common.h"
 #include "varcoef.h"
 
@@ -32,16 +43,30 @@ template <typename T> __device__ __forceinline__ T vfma(T a, T b, T c);
 template <> __device__ __forceinline__ float vfma<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 template <> __device__ __forceinline__ double vfma<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// What a kernel needs of VarcoefArgs.
+struct VarcoefGeo {
+  int nx, ny, nz, zc;
+  int tiles_x, tiles_y, nblocks;
+  const void* c;
+  const void* d;
+  const void* m;
+  void* y;
+};
+
 template <int N, typename T, int BC>
-__global__ __launch_bounds__(64) void varcoef_kernel(VarcoefArgs a, VarcoefTabF tf) {
+__global__ __launch_bounds__(64 * kVcWaves) void varcoef_kernel(VarcoefGeo a, VarcoefTab<T> tab) {
   constexpr int Q = (3 * N + 2) / 2;
   constexpr int NB = N + 1;
+  constexpr int NP = NB / 2, NE = (NB + 1) / 2;  // pairs (t, n - t); even parts (with the middle B-spline)
+  constexpr int QP = Q / 2;                      // pairs (q, Q - 1 - q) of points
   constexpr int H = N / 2;
   constexpr int TXO = 64 - 2 * N;
-  constexpr int TY = kVcTileY;
-  __shared__ T acc[TY * NB * 64];  // [output row][plane slot][lane]: each lane owns its column
+  constexpr int TY = vc_tile_y(sizeof(T) == 8 ? 0 : 1);
+  __shared__ T acc[TY * NB * 64];            // [output row][plane slot][lane]; wave r % kVcWaves owns row r
+  __shared__ T rows[kVcWaves][TY][2][64];    // y-projected rows of the waves' current z-points
 
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bid = xcd_remap(blockIdx.x, a.nblocks);
   const int txi = bid % a.tiles_x;
   const int rest = bid / a.tiles_x;
@@ -55,12 +80,6 @@ __global__ __launch_bounds__(64) void varcoef_kernel(VarcoefArgs a, VarcoefTabF 
   const T* __restrict__ Dc = (const T*)a.d;
   const T* __restrict__ Mc = (const T*)a.m;
   T* __restrict__ Y = (T*)a.y;
-
-  // basis tables (uniform): value / derivative of B-spline t of a cell at Gauss point q, weights
-  auto BV = [&](int q, int t) -> T { return sizeof(T) == 8 ? (T)a.bv[q * kVcMaxB + t] : (T)tf.bv[q * kVcMaxB + t]; };
-  auto BD = [&](int q, int t) -> T { return sizeof(T) == 8 ? (T)a.bd[q * kVcMaxB + t] : (T)tf.bd[q * kVcMaxB + t]; };
-  auto WQ = [&](int q) -> T { return sizeof(T) == 8 ? (T)a.w[q] : (T)tf.w[q]; };
-  const T ihx2 = (T)a.ihx2, ihy2 = (T)a.ihy2, ihz2 = (T)a.ihz2;
 
   // this lane's coefficient column: c is read there (zero outside a Dirichlet box), mu and D at
   // the nearest column inside (their expansions continue by the edge coefficients)
@@ -77,38 +96,43 @@ __global__ __launch_bounds__(64) void varcoef_kernel(VarcoefArgs a, VarcoefTabF 
     xcm = min(max(xp, 0), nx - 1);
   }
 
-  for (int i = lane; i < TY * NB * 64; i += 64) acc[i] = (T)0;
+  for (int r = wave; r < TY; r += kVcWaves)
+#pragma unroll
+    for (int t = 0; t < NB; ++t) acc[(r * NB + t) * 64 + lane] = (T)0;
 
   const int jz0 = z0 + H - N, jz1 = z0 + zc_eff + H;  // z-cells whose support meets the chunk
   const int jy0 = y0 + H - N;                        // first y-cell of the strip's rows
-  for (int jz = jz0; jz < jz1; ++jz) {
-    // the n+1 coefficient planes of this z-cell
-    int64_t pcz[NB], pmz[NB];
-    bool zok[NB];
+  // tasks in the order (z-cell, z-point), kVcWaves at a time
+  const int ntask = (jz1 - jz0) * Q;
+  for (int task0 = 0; task0 < ntask; task0 += kVcWaves) {
+    const int task = task0 + wave;
+    if (task < ntask) {
+      const int jz = jz0 + task / Q, zq = task % Q;
+      // the n+1 coefficient planes of this z-cell
+      int64_t pcz[NB], pmz[NB];
+      bool zok[NB];
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      const int kz = jz - H + t;
-      int kc, km;
-      if (BC == BC_PERIODIC) {
-        kc = ((kz % nz) + nz) % nz;
-        km = kc;
-        zok[t] = true;
-      } else {
-        zok[t] = kz >= 0 && kz < nz;
-        kc = zok[t] ? kz : 0;
-        km = min(max(kz, 0), nz - 1);
+      for (int t = 0; t < NB; ++t) {
+        const int kz = jz - H + t;
+        int kc, km;
+        if (BC == BC_PERIODIC) {
+          kc = ((kz % nz) + nz) % nz;
+          km = kc;
+          zok[t] = true;
+        } else {
+          zok[t] = kz >= 0 && kz < nz;
+          kc = zok[t] ? kz : 0;
+          km = min(max(kz, 0), nz - 1);
+        }
+        pcz[t] = (int64_t)kc * plane;
+        pmz[t] = (int64_t)km * plane;
       }
-      pcz[t] = (int64_t)kc * plane;
-      pmz[t] = (int64_t)km * plane;
-    }
-    for (int zq = 0; zq < Q; ++zq) {
       T bzv[NB], bzd[NB];
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
-        bzv[t] = BV(zq, t);
-        bzd[t] = BD(zq, t);
+        bzv[t] = tab.v[zq][t];
+        bzd[t] = tab.d[zq][t];
       }
-      const T wz = WQ(zq);
       // fields at (z-point zq, coefficient row ky, this column): c value, c z-derivative, mu, D
       auto load_row = [&](int ky, T* out) {
         int kc, km;
@@ -146,84 +170,118 @@ __global__ __launch_bounds__(64) void varcoef_kernel(VarcoefArgs a, VarcoefTabF 
       for (int s = 0; s < TY + N; ++s) {
         const int jy = jy0 + s;
         load_row(jy - H + N, zr[N]);
-#pragma unroll
+#pragma unroll 1
         for (int yq = 0; yq < Q; ++yq) {
           // y-interpolation: c (value, y-derivative), c_z, mu, D at (yq, zq) in this column
-          T f0 = (T)0, f1 = (T)0, f2 = (T)0, f3 = (T)0, f4 = (T)0;
+          T f[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
 #pragma unroll
           for (int t = 0; t < NB; ++t) {
-            const T bv = BV(yq, t), bd = BD(yq, t);
-            f0 = vfma(bv, zr[t][0], f0);
-            f1 = vfma(bd, zr[t][0], f1);
-            f2 = vfma(bv, zr[t][1], f2);
-            f3 = vfma(bv, zr[t][2], f3);
-            f4 = vfma(bv, zr[t][3], f4);
+            const T bv = tab.v[yq][t], bd = tab.d[yq][t];
+            f[0] = vfma(bv, zr[t][0], f[0]);
+            f[1] = vfma(bd, zr[t][0], f[1]);
+            f[2] = vfma(bv, zr[t][1], f[2]);
+            f[3] = vfma(bv, zr[t][2], f[3]);
+            f[4] = vfma(bv, zr[t][3], f[4]);
           }
-          // the cell of this lane uses columns lane .. lane + n
-          T nb[NB][5];
-          nb[0][0] = f0; nb[0][1] = f1; nb[0][2] = f2; nb[0][3] = f3; nb[0][4] = f4;
+          // the cell of this lane uses columns lane .. lane + n: sums and differences of the pairs
+          T fe[NE][5], fo[NP][5];
 #pragma unroll
-          for (int t = 1; t < NB; ++t) {
-            nb[t][0] = __shfl_down(f0, t, 64);
-            nb[t][1] = __shfl_down(f1, t, 64);
-            nb[t][2] = __shfl_down(f2, t, 64);
-            nb[t][3] = __shfl_down(f3, t, 64);
-            nb[t][4] = __shfl_down(f4, t, 64);
-          }
-          const T wyz = WQ(yq) * wz;
-          T pa[NB], pb[NB], pc[NB];
+          for (int i = 0; i < 5; ++i) {
+            T nb[NB];
+            nb[0] = f[i];
 #pragma unroll
-          for (int t = 0; t < NB; ++t) pa[t] = pb[t] = pc[t] = (T)0;
+            for (int t = 1; t < NB; ++t) nb[t] = __shfl_down(f[i], t, 64);
 #pragma unroll
-          for (int xq = 0; xq < Q; ++xq) {
-            T phi = (T)0, phx = (T)0, phy = (T)0, phz = (T)0, mu = (T)0, dd = (T)0;
-#pragma unroll
-            for (int t = 0; t < NB; ++t) {
-              const T bv = BV(xq, t), bd = BD(xq, t);
-              phi = vfma(bv, nb[t][0], phi);
-              phx = vfma(bd, nb[t][0], phx);
-              phy = vfma(bv, nb[t][1], phy);
-              phz = vfma(bv, nb[t][2], phz);
-              mu = vfma(bv, nb[t][3], mu);
-              dd = vfma(bv, nb[t][4], dd);
+            for (int t = 0; t < NP; ++t) {
+              fe[t][i] = nb[t] + nb[N - t];
+              fo[t][i] = nb[t] - nb[N - t];
             }
-            const T wq = WQ(xq) * wyz;
-            const T g0 = wq * mu * phi;
-            const T wd = wq * dd;
-            const T g1 = wd * ihx2 * phx, g2 = wd * ihy2 * phy, g3 = wd * ihz2 * phz;
+            if (NB % 2) fe[NE - 1][i] = nb[NB / 2];
+          }
+          // even and odd sums of the projections: pa (value and x-derivative tests), pb, pc (value tests)
+          T ae[NE], ao[NP], be[NE], bo[NP], ce[NE], co[NP];
 #pragma unroll
-            for (int t = 0; t < NB; ++t) {
-              const T bv = BV(xq, t), bd = BD(xq, t);
-              pa[t] = vfma(bv, g0, vfma(bd, g1, pa[t]));
-              pb[t] = vfma(bv, g2, pb[t]);
-              pc[t] = vfma(bv, g3, pc[t]);
+          for (int t = 0; t < NE; ++t) ae[t] = be[t] = ce[t] = (T)0;
+#pragma unroll
+          for (int t = 0; t < NP; ++t) ao[t] = bo[t] = co[t] = (T)0;
+#pragma unroll
+          for (int q = 0; q < QP + Q % 2; ++q) {
+            // even (E) and odd (O) parts of phi, phi_y, phi_z, mu, D and (XE, XO) of phi_x
+            T E[5], O[5], XE = (T)0, XO = (T)0;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+              E[i] = tab.xve[q][0] * fe[0][i];
+#pragma unroll
+              for (int t = 1; t < NE; ++t) E[i] = vfma(tab.xve[q][t], fe[t][i], E[i]);
+              O[i] = (T)0;
+              if (q < QP) {
+                O[i] = tab.xvo[q][0] * fo[0][i];
+#pragma unroll
+                for (int t = 1; t < NP; ++t) O[i] = vfma(tab.xvo[q][t], fo[t][i], O[i]);
+              }
+            }
+#pragma unroll
+            for (int t = 0; t < NP; ++t) XO = vfma(tab.xdo[q][t], fo[t][0], XO);
+            if (q < QP) {
+#pragma unroll
+              for (int t = 0; t < NE; ++t) XE = vfma(tab.xde[q][t], fe[t][0], XE);
+              // points q and Q - 1 - q
+              const T mu0 = E[3] + O[3], mu1 = E[3] - O[3], d0 = E[4] + O[4], d1 = E[4] - O[4];
+              const T a0 = mu0 * (E[0] + O[0]), a1 = mu1 * (E[0] - O[0]);
+              const T x0 = d0 * (XO + XE), x1 = d1 * (XO - XE);
+              const T b0 = d0 * (E[1] + O[1]), b1 = d1 * (E[1] - O[1]);
+              const T c0 = d0 * (E[2] + O[2]), c1 = d1 * (E[2] - O[2]);
+              const T as = a0 + a1, ad = a0 - a1, xs = x0 + x1, xd = x0 - x1;
+              const T bs = b0 + b1, bd = b0 - b1, cs = c0 + c1, cd = c0 - c1;
+#pragma unroll
+              for (int t = 0; t < NE; ++t) {
+                ae[t] = vfma(tab.pve[q][t], as, vfma(tab.pde[q][t], xd, ae[t]));
+                be[t] = vfma(tab.pve[q][t], bs, be[t]);
+                ce[t] = vfma(tab.pve[q][t], cs, ce[t]);
+              }
+#pragma unroll
+              for (int t = 0; t < NP; ++t) {
+                ao[t] = vfma(tab.pvo[q][t], ad, vfma(tab.pdo[q][t], xs, ao[t]));
+                bo[t] = vfma(tab.pvo[q][t], bd, bo[t]);
+                co[t] = vfma(tab.pvo[q][t], cd, co[t]);
+              }
+            } else {
+              // the middle point: even value parts and odd derivative parts only
+              const T a0 = E[3] * E[0], x0 = E[4] * XO, b0 = E[4] * E[1], c0 = E[4] * E[2];
+#pragma unroll
+              for (int t = 0; t < NE; ++t) {
+                ae[t] = vfma(tab.pve[q][t], a0, ae[t]);
+                be[t] = vfma(tab.pve[q][t], b0, be[t]);
+                ce[t] = vfma(tab.pve[q][t], c0, ce[t]);
+              }
+#pragma unroll
+              for (int t = 0; t < NP; ++t) ao[t] = vfma(tab.pdo[q][t], x0, ao[t]);
             }
           }
           // x-projection: output column o collects partial t of the cell in lane o - t
-          T ax = pa[0], bx = pb[0], cx = pc[0];
+          auto part = [&](const T* e, const T* o, int t) -> T {
+            return t < NP ? e[t] + o[t] : (NB % 2 && t == NB / 2 ? e[NE - 1] : e[N - t] - o[N - t]);
+          };
+          T ax = part(ae, ao, 0), bx = part(be, bo, 0), cx = part(ce, co, 0);
 #pragma unroll
           for (int t = 1; t < NB; ++t) {
-            ax += __shfl_up(pa[t], t, 64);
-            bx += __shfl_up(pb[t], t, 64);
-            cx += __shfl_up(pc[t], t, 64);
+            ax += __shfl_up(part(ae, ao, t), t, 64);
+            bx += __shfl_up(part(be, bo, t), t, 64);
+            cx += __shfl_up(part(ce, co, t), t, 64);
           }
           // y-projection onto the cell's n+1 output rows
 #pragma unroll
           for (int t = 0; t < NB; ++t) {
-            const T bv = BV(yq, t), bd = BD(yq, t);
+            const T bv = tab.pv[yq][t], bd = tab.pdy[yq][t];
             ya[t] = vfma(bv, ax, vfma(bd, bx, ya[t]));
             yc[t] = vfma(bv, cx, yc[t]);
           }
         }
-        // output row jy - H has all its y-cells for this z-point: z-projection into its planes
+        // output row jy - H has all its y-cells for this z-point
         const int r = jy - H - y0;
         if (r >= 0 && r < TY) {
-#pragma unroll
-          for (int t = 0; t < NB; ++t) {
-            const int slot = (((jz - H + t) % NB) + NB) % NB;
-            T* p = &acc[(r * NB + slot) * 64 + lane];
-            *p = vfma(bzv[t], ya[0], vfma(bzd[t], yc[0], *p));
-          }
+          rows[wave][r][0][lane] = ya[0];
+          rows[wave][r][1][lane] = yc[0];
         }
 #pragma unroll
         for (int t = 0; t < N; ++t) {
@@ -235,41 +293,85 @@ __global__ __launch_bounds__(64) void varcoef_kernel(VarcoefArgs a, VarcoefTabF 
         ya[N] = yc[N] = (T)0;
       }
     }
-    // output plane jz - H has all its z-cells: write it and clear its slot
-    const int kz = jz - H;
-    const int slot = ((kz % NB) + NB) % NB;
-    const bool wcol = lane >= N && lane < N + TXO && xp < nx && kz >= z0 && kz < z0 + zc_eff;
-    for (int r = 0; r < TY; ++r) {
-      T* p = &acc[(r * NB + slot) * 64 + lane];
-      if (wcol && y0 + r < ny) Y[(int64_t)kz * plane + (int64_t)(y0 + r) * nx + xp] = *p;
-      *p = (T)0;
+    __syncthreads();
+    // z-projection of the finished z-points, in order; each wave its own rows
+    for (int w = 0; w < kVcWaves && task0 + w < ntask; ++w) {
+      const int jz = jz0 + (task0 + w) / Q, zq = (task0 + w) % Q;
+      for (int r = wave; r < TY; r += kVcWaves) {
+        const T va = rows[w][r][0][lane], vc = rows[w][r][1][lane];
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+          const int slot = (((jz - H + t) % NB) + NB) % NB;
+          T* p = &acc[(r * NB + slot) * 64 + lane];
+          *p = vfma(tab.pv[zq][t], va, vfma(tab.pdz[zq][t], vc, *p));
+        }
+      }
+      if (zq == Q - 1) {
+        // output plane jz - H has all its z-cells: write it and clear its slot
+        const int kz = jz - H;
+        const int slot = ((kz % NB) + NB) % NB;
+        const bool wcol = lane >= N && lane < N + TXO && xp < nx && kz >= z0 && kz < z0 + zc_eff;
+        for (int r = wave; r < TY; r += kVcWaves) {
+          T* p = &acc[(r * NB + slot) * 64 + lane];
+          if (wcol && y0 + r < ny) Y[(int64_t)kz * plane + (int64_t)(y0 + r) * nx + xp] = *p;
+          *p = (T)0;
+        }
+      }
     }
+    __syncthreads();  // the rows are read before the next points overwrite them
   }
 }
 
 template <int N, typename T>
-static hipError_t launch_nt(const VarcoefArgs& a, const VarcoefTabF& tf, int bc, hipStream_t st) {
+static hipError_t launch_nt(const VarcoefArgs& a, int bc, hipStream_t st) {
+  constexpr int Q = (3 * N + 2) / 2, NB = N + 1, NP = NB / 2;
+  const VarcoefGeo g{a.nx, a.ny, a.nz, a.zc, a.tiles_x, a.tiles_y, a.nblocks, a.c, a.d, a.m, a.y};
+  VarcoefTab<T> tab{};
+  auto bv = [&](int q, int t) { return a.bv[q * kVcMaxB + t]; };
+  auto bd = [&](int q, int t) { return a.bd[q * kVcMaxB + t]; };
+  for (int q = 0; q < Q; ++q)
+    for (int t = 0; t < NB; ++t) {
+      tab.v[q][t] = (T)bv(q, t);
+      tab.d[q][t] = (T)bd(q, t);
+      tab.pv[q][t] = (T)(a.w[q] * bv(q, t));
+      tab.pdy[q][t] = (T)(a.w[q] * bd(q, t) * a.ihy2);
+      tab.pdz[q][t] = (T)(a.w[q] * bd(q, t) * a.ihz2);
+    }
+  for (int q = 0; q < (Q + 1) / 2; ++q) {
+    for (int t = 0; t < NP; ++t) {
+      const double ve = 0.5 * (bv(q, t) + bv(q, N - t)), vo = 0.5 * (bv(q, t) - bv(q, N - t));
+      const double de = 0.5 * (bd(q, t) + bd(q, N - t)), dv = 0.5 * (bd(q, t) - bd(q, N - t));
+      tab.xve[q][t] = (T)ve;
+      tab.xvo[q][t] = (T)vo;
+      tab.xde[q][t] = (T)de;
+      tab.xdo[q][t] = (T)dv;
+      tab.pve[q][t] = (T)(a.w[q] * ve);
+      tab.pvo[q][t] = (T)(a.w[q] * vo);
+      tab.pde[q][t] = (T)(a.w[q] * de * a.ihx2);
+      tab.pdo[q][t] = (T)(a.w[q] * dv * a.ihx2);
+    }
+    if (NB % 2) {
+      tab.xve[q][NP] = (T)bv(q, NP);
+      tab.xde[q][NP] = (T)bd(q, NP);
+      tab.pve[q][NP] = (T)(a.w[q] * bv(q, NP));
+      tab.pde[q][NP] = (T)(a.w[q] * bd(q, NP) * a.ihx2);
+    }
+  }
   if (bc == BC_PERIODIC)
-    hipLaunchKernelGGL((varcoef_kernel<N, T, BC_PERIODIC>), dim3(a.nblocks), dim3(64), 0, st, a, tf);
+    hipLaunchKernelGGL((varcoef_kernel<N, T, BC_PERIODIC>), dim3(a.nblocks), dim3(64 * kVcWaves), 0, st, g, tab);
   else
-    hipLaunchKernelGGL((varcoef_kernel<N, T, BC_DIRICHLET>), dim3(a.nblocks), dim3(64), 0, st, a, tf);
+    hipLaunchKernelGGL((varcoef_kernel<N, T, BC_DIRICHLET>), dim3(a.nblocks), dim3(64 * kVcWaves), 0, st, g, tab);
   return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t launch_t(const VarcoefArgs& a, int n, int bc, hipStream_t st) {
-  VarcoefTabF tf;
-  for (int i = 0; i < kVcMaxQ * kVcMaxB; ++i) {
-    tf.bv[i] = (float)a.bv[i];
-    tf.bd[i] = (float)a.bd[i];
-  }
-  for (int i = 0; i < kVcMaxQ; ++i) tf.w[i] = (float)a.w[i];
   switch (n) {
-    case 1: return launch_nt<1, T>(a, tf, bc, st);
-    case 2: return launch_nt<2, T>(a, tf, bc, st);
-    case 3: return launch_nt<3, T>(a, tf, bc, st);
-    case 4: return launch_nt<4, T>(a, tf, bc, st);
-    case 5: return launch_nt<5, T>(a, tf, bc, st);
+    case 1: return launch_nt<1, T>(a, bc, st);
+    case 2: return launch_nt<2, T>(a, bc, st);
+    case 3: return launch_nt<3, T>(a, bc, st);
+    case 4: return launch_nt<4, T>(a, bc, st);
+    case 5: return launch_nt<5, T>(a, bc, st);
   }
   return hipErrorInvalidValue;
 }
