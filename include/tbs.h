@@ -89,7 +89,7 @@ typedef struct {
                               bf16-stored direction); a sweep asks for max(inner_rtol, rtol / (2 rel)) */
   int inner_max_iter;      /* refinement: inner iteration cap per sweep (default 500) */
   int max_sweeps;          /* refinement: sweep cap (default 12) */
-  int poll_every;          /* CG iterations enqueued between host convergence polls (default 4).
+  int poll_every;          /* CG iterations enqueued ahead of the host's convergence poll (default 4).
                               0 = tbs_cg_step polls never: it enqueues all n_iters iterations (those
                               after convergence return at once on the device) and the flush, and
                               with NULL rel_res_out and iters_out nothing in tbs_cg_begin +
@@ -257,8 +257,9 @@ int tbs_cg_begin(tbs_ctx* ctx, const void* b, void* x, int dtype, double rtol);
 /* Runs up to n_iters more CG iterations (the form tbs_opts.fused_cg selects: one kernel per
  * iteration, or the two-kernel Hestenes-Stiefel iteration) and stops once ||r|| <= rtol ||b||, r
  * being the recursive residual (one-kernel form: its one-step prediction), leaving x consistent.
- * It polls the device's convergence flag every tbs_opts.poll_every iterations (which synchronises);
- * with poll_every 0 it enqueues all n_iters and never waits.  If rel_res_out is not NULL it receives
+ * It polls the device's convergence flag, at most tbs_opts.poll_every iterations ahead of it (which
+ * waits for the device); with poll_every 0 it enqueues all n_iters and never waits.  If rel_res_out is
+ * not NULL it receives
  * ||r||/||b|| and iters_out the total iteration count (both synchronise).  Returns
  * TBS_E_BREAKDOWN on p^T A p <= 0 or non-finite values (with polling). */
 int tbs_cg_step(tbs_ctx* ctx, int n_iters, double* rel_res_out, int* iters_out);

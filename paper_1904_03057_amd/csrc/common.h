@@ -12,7 +12,8 @@ struct Taps {
   double ax, ay, az, tau;
 };
 
-// Device-resident solver scalars (written only by the single-block finalize kernels).
+// Device-resident solver scalars (written by the single-block finalize kernels and by the last
+// workgroup of a one-kernel CG iteration).
 struct Scalars {
   double rr;      // r.r of the current recursive residual
   double pq;      // p.Ap of the current iteration
@@ -33,6 +34,9 @@ struct Scalars {
   // 1: x is zero and not read (set by FIN_INIT_XZERO; the first x update writes it, the x-update
   // kernels and the refinement update take it as zero until then)
   int xzero;
+  // workgroups of the running one-kernel CG iteration that have written their partial sums; the last
+  // one forms the scalars and clears it (its own cache line: the other members are read plainly)
+  alignas(128) unsigned ticket;
 };
 static_assert(sizeof(Scalars) <= 256, "a Scalars slot of the workspace is 256 bytes");
 
@@ -71,7 +75,9 @@ struct StencilArgs {
   double* part1;               // RESID: b.b  CGF: r.q
   double* part2;               // CGF: q.q
   double* part3;               // CGF: r.r (of r_new)
-  const Scalars* scal;         // CG1, CGF: alpha, beta, done, pending
+  Scalars* scal;               // CG1, CGF: alpha, beta, done, pending (CGF also writes them)
+  unsigned long long* status;  // CGF: host word that gets the progress after each launch (nullable)
+  unsigned gen;                // CGF: tag of the solve in that word
   int first;                   // CG1, CGF: first iteration (p = r)
   int order;                   // tile order: 0 x-tiles fastest, 1 y-tiles fastest
   int nt_store;                // 1: outputs written with non-temporal stores
@@ -125,6 +131,39 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+// One-kernel CG: the scalars after iteration k from v0 = p_k.q_k, v1 = r_k.q_k, v2 = q_k.q_k and v3 =
+// r_k.r_k of the iteration's recursive residual.  alpha from the explicit r_k.r_k; r_{k+1}.r_{k+1} =
+// r.r - 2 alpha r.q + alpha^2 q.q (one step ahead, restarted from the explicit value every iteration)
+// gives beta and the stopping test.  The kernel applied the pending x updates only if there were two;
+// this iteration's is added.
+__device__ __forceinline__ void cg_fused_update(Scalars* s, double v0, double v1, double v2, double v3) {
+  if (s->pending == 2) { s->pending = 0; s->xzero = 0; }  // x was written
+  s->pq = v0;
+  if (!(v0 > 0.0) || !isfinite(v0) || !isfinite(v1) || !isfinite(v2) || !isfinite(v3)) {
+    s->status = -4;
+    s->done = 1;
+    return;
+  }
+  const double alpha = v3 / v0;
+  double rn = v3 - 2.0 * alpha * v1 + alpha * alpha * v2;
+  if (rn < 0.0) rn = 0.0;
+  s->alpha2 = s->alpha;
+  s->alpha = alpha;
+  s->beta = v3 > 0.0 ? rn / v3 : 0.0;
+  s->rr = rn;
+  s->nit += 1;
+  s->pending += 1;
+  if (rn <= s->tol2) s->done = 1;
+}
+
+// Progress of a one-kernel CG solve as the host reads it: iterations (bits 0-31), done (32), breakdown
+// (33), tag of the solve (48-63).
+__device__ __forceinline__ void cg_publish(unsigned long long* word, unsigned gen, const Scalars* s) {
+  const unsigned long long v = (unsigned long long)(unsigned)s->nit | ((unsigned long long)(s->done != 0) << 32) |
+                               ((unsigned long long)(s->status != 0) << 33) | ((unsigned long long)gen << 48);
+  __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Block-to-tile map that keeps consecutive logical tiles on one XCD (blocks are dealt to the

@@ -208,45 +208,38 @@ __global__ void norms_out_kernel(const Scalars* __restrict__ s, double* __restri
 }
 
 __global__ __launch_bounds__(1024) void finalize_kernel(int op, const double* __restrict__ p0,
-                                                        const double* __restrict__ p1,
-                                                        const double* __restrict__ p2,
-                                                        const double* __restrict__ p3, int count, Scalars* s,
+                                                        const double* __restrict__ p1, int count, Scalars* s,
                                                         double rtol) {
-  __shared__ double r0[1024], r1[1024], r2[1024], r3[1024];
+  __shared__ double r0[1024], r1[1024];
   if (op == FIN_CLEAR_PENDING) {
     if (threadIdx.x == 0) s->pending = 0;
     return;
   }
-  if ((op == FIN_ALPHA || op == FIN_BETA || op == FIN_FUSED) && s->done) return;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  if ((op == FIN_ALPHA || op == FIN_BETA) && s->done) return;
+  double a0 = 0.0, a1 = 0.0;
   for (int i = threadIdx.x; i < count; i += 1024) {
     a0 += p0[i];
     if (p1) a1 += p1[i];
-    if (p2) a2 += p2[i];
-    if (p3) a3 += p3[i];
   }
   r0[threadIdx.x] = a0;
   r1[threadIdx.x] = a1;
-  r2[threadIdx.x] = a2;
-  r3[threadIdx.x] = a3;
   __syncthreads();
   for (int w = 512; w > 0; w >>= 1) {
     if (threadIdx.x < w) {
       r0[threadIdx.x] += r0[threadIdx.x + w];
       r1[threadIdx.x] += r1[threadIdx.x + w];
-      r2[threadIdx.x] += r2[threadIdx.x + w];
-      r3[threadIdx.x] += r3[threadIdx.x + w];
     }
     __syncthreads();
   }
   if (threadIdx.x != 0) return;
-  const double v0 = r0[0], v1 = r1[0], v2 = r2[0], v3 = r3[0];
+  const double v0 = r0[0], v1 = r1[0];
   switch (op) {
     case FIN_INIT:
     case FIN_INIT_XZERO: {
       s->rr = v0; s->rr0 = v0; s->bb = v1; s->tol2 = rtol * rtol * v1;
       s->nit = 0; s->status = 0; s->pending = 0; s->alpha = 0.0; s->alpha2 = 0.0; s->beta = 0.0;
       s->xzero = (op == FIN_INIT_XZERO);
+      s->ticket = 0;
       int done = (v1 == 0.0) || (v0 <= s->tol2);
       if (!isfinite(v0) || !isfinite(v1)) { s->status = -4; done = 1; }
       s->done = done;
@@ -266,28 +259,6 @@ __global__ __launch_bounds__(1024) void finalize_kernel(int op, const double* __
       s->nit += 1;
       s->pending = 1;
       if (v0 <= s->tol2) s->done = 1;
-      break;
-    }
-    case FIN_FUSED: {
-      // v0 = p_k.q_k, v1 = r_k.q_k, v2 = q_k.q_k, v3 = r_k.r_k of the iteration's recursive residual.
-      // alpha from the explicit r_k.r_k; r_{k+1}.r_{k+1} = r.r - 2 alpha r.q + alpha^2 q.q (one step
-      // ahead, restarted from the explicit value every iteration) gives beta and the stopping test.
-      // The kernel applied the pending x updates only if there were two; this iteration's is added.
-      if (s->pending == 2) { s->pending = 0; s->xzero = 0; }  // x was written
-      s->pq = v0;
-      if (!(v0 > 0.0) || !isfinite(v0) || !isfinite(v1) || !isfinite(v2) || !isfinite(v3)) {
-        s->status = -4; s->done = 1; break;
-      }
-      const double alpha = v3 / v0;
-      double rn = v3 - 2.0 * alpha * v1 + alpha * alpha * v2;
-      if (rn < 0.0) rn = 0.0;
-      s->alpha2 = s->alpha;
-      s->alpha = alpha;
-      s->beta = v3 > 0.0 ? rn / v3 : 0.0;
-      s->rr = rn;
-      s->nit += 1;
-      s->pending += 1;
-      if (rn <= s->tol2) s->done = 1;
       break;
     }
     case FIN_DOT: s->out = v0; break;
@@ -406,8 +377,8 @@ hipError_t launch_norms_out(const Scalars* s, double* out, hipStream_t st) {
 }
 
 hipError_t launch_finalize(int op, const double* p0, const double* p1, int count, Scalars* s, double rtol,
-                           hipStream_t st, const double* p2, const double* p3) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, st, op, p0, p1, p2, p3, count, s, rtol);
+                           hipStream_t st) {
+  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, st, op, p0, p1, count, s, rtol);
   return hipGetLastError();
 }
 
