@@ -282,9 +282,9 @@ int tbs_timestep(tbs_ctx* ctx, const double* u_prev, const double* q, double* u_
  * s_k = sum_l c_l b^n(k - l) with the sampled B-spline b^n_k = beta^n(k), tensor product over the
  * three axes; the direct transform inverts it, c = (b^n)^{-1} * s.  Same grid layout and boundary
  * conditions as the operator: periodic = circular convolution, Dirichlet = coefficients outside
- * the box are zero (truncated band).  The paper applies the inverse by recursive filtering; here
- * the direct transform is the FP64 CG solve of E c = s with E applied on the fly (E is SPD with
- * condition number below 8^3 for degrees 2..5), which reaches the same exact solution. */
+ * the box are zero (truncated band).  The direct transform inverts E along each axis by recursive
+ * filtering, as the paper does, on the FP64 residual E c - s (E is SPD with condition number below 8^3
+ * for degrees 2..5). */
 
 /* Creates a transform context for an Nx x Ny x Nz grid and spline degree 2..5 (each N_d >=
  * 2 floor(degree/2) + 1), boundary condition bc, HIP stream.  tbs_destroy releases it;
@@ -296,11 +296,12 @@ int tbs_transform_setup(tbs_ctx** out, const int64_t grid[3], int degree, int bc
  * 256-byte aligned, not aliased).  Asynchronous.  TBS_E_STATE on a solver context. */
 int tbs_transform_eval(tbs_ctx* ctx, const void* coef, void* samples, int dtype);
 
-/* Direct transform: solves E coef = samples in FP64 by CG, stopping when the recursive residual
- * satisfies ||r|| <= rtol ||samples||, starting from the values coef holds on entry (a copy of the
- * samples is a good start).  *iters and *rel_res (nullable) receive the CG iterations and the
- * true FP64 relative residual recomputed at exit (near FP64 precision it can exceed rtol
- * slightly).  Synchronises.  Returns TBS_OK, TBS_W_NOT_CONVERGED or TBS_E_BREAKDOWN. */
+/* Direct transform: solves E coef = samples in FP64, stopping when the residual satisfies
+ * ||samples - E coef|| <= rtol ||samples|| (or, for rtol > 0, when it has reached its rounding level),
+ * starting from the values coef holds on entry (a copy of the samples is a good start).  *iters and
+ * *rel_res (nullable) receive the number of separable solves (at most max_iter; one usually does) and the
+ * FP64 relative residual at exit (near FP64 precision it can exceed rtol slightly).  Synchronises.
+ * Returns TBS_OK, TBS_W_NOT_CONVERGED or TBS_E_BREAKDOWN (non-finite values). */
 int tbs_transform_interp(tbs_ctx* ctx, const double* samples, double* coef, double rtol, int max_iter,
                          int* iters, double* rel_res);
 

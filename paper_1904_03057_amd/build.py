@@ -22,7 +22,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 STENCIL_UNITS = [("stencil_inst.hip", "stencil_n%d_%s" % (n, b.lower()), ["-DTBS_DEGREE=%d" % n, "-DTBS_BC=BC_%s" % b])
                  for n in (5, 4, 3, 2, 1) for b in ("ROBIN", "DIRICHLET", "PERIODIC")]
 SOURCES = STENCIL_UNITS + [(f, f, []) for f in ("stencil.hip", "vector.hip", "net.hip", "transfer.hip",
-                                                "varcoef.hip", "api.cpp")]
+                                                "varcoef.hip", "bsolve.hip", "api.cpp")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
