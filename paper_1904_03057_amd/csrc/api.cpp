@@ -157,6 +157,9 @@ struct tbs_ctx {
   hipStream_t st;
   Taps taps;
   int zc[M_RHSRES + 1][2];  // planes per z-chunk of each stencil mode, in FP32 and FP64
+  // the one-kernel CG iteration: z-chunk and tile shape in FP32 and FP64 (a bf16-stored direction takes
+  // shape 0 and zc[M_CGF])
+  int cgf_zc[2], cgf_shape[2];
   int nparts;               // partial sums of the largest launch
   char* ws;
   size_t ws_bytes;
@@ -189,17 +192,22 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 static bool aligned_ptr(const void* p) { return p && ((uintptr_t)p & 255u) == 0; }
 
 static StencilArgs base_args(const tbs_ctx* c, int mode, int compute_bytes);
+static StencilArgs cgf_args(const tbs_ctx* c, int dt);
 
 static void plan_geometry(tbs_ctx* c, int zchunk) {
   c->nparts = kVecBlocks;
-  for (int mode = M_APPLY; mode <= M_RHSRES; ++mode)
-    for (int f64 = 0; f64 < 2; ++f64) {
-      const int es = f64 ? 8 : 4;
+  for (int f64 = 0; f64 < 2; ++f64) {
+    const int es = f64 ? 8 : 4;
+    for (int mode = M_APPLY; mode <= M_RHSRES; ++mode) {
       // RHSRES stands in for RESID: the same launch shape, so that its partial sums do too
-      c->zc[mode][f64] = stencil_plan_zc(c->nx, c->ny, c->nz, mode == M_RHSRES ? M_RESID : mode, es, c->n, c->bc, zchunk);
+      c->zc[mode][f64] = stencil_plan_zc(c->nx, c->ny, c->nz, mode == M_RHSRES ? M_RESID : mode, es, c->n, c->bc, zchunk,
+                                         nullptr);
       if (mode == M_CG1 || mode == M_CGF || (f64 && (mode == M_RESID || mode == M_RHSRES)))
         c->nparts = std::max(c->nparts, stencil_blocks(base_args(c, mode, es), mode, es, c->n, c->bc));
     }
+    c->cgf_zc[f64] = stencil_plan_zc(c->nx, c->ny, c->nz, M_CGF, es, c->n, c->bc, zchunk, &c->cgf_shape[f64]);
+    c->nparts = std::max(c->nparts, stencil_blocks(cgf_args(c, f64 ? 0 : 1), M_CGF, es, c->n, c->bc));
+  }
 }
 
 // workspace layout: [scalars x4][part0][part1][part2][part3][arrays...]
@@ -263,6 +271,17 @@ static StencilArgs base_args(const tbs_ctx* c, int mode, int compute_bytes) {
   a.order = c->opts.tile_order;
   a.nt_store = c->opts.nt_store;
   if (c->bc == TBS_BC_ROBIN) a.rb = c->rb;
+  return a;
+}
+
+// of a one-kernel CG iteration (dt 0: FP64, 1: FP32, 2: FP32 with bf16 p)
+static StencilArgs cgf_args(const tbs_ctx* c, int dt) {
+  StencilArgs a = base_args(c, M_CGF, dt == 0 ? 8 : 4);
+  if (dt != 2) {
+    a.shape = c->cgf_shape[dt == 0];
+    a.zc = c->cgf_zc[dt == 0];
+    a.nchunks = (int)((c->nz + a.zc - 1) / a.zc);
+  }
   return a;
 }
 
@@ -801,7 +820,7 @@ static int cg1_async(tbs_ctx* c, const CgArrays& A, int dt, int k) {
 // updates).  r, p and q alternate between two arrays (halo reads of the old values and writes of
 // the new ones overlap in one launch).
 static int cgf_async(tbs_ctx* c, const CgArrays& A, int dt, int k, bool publish) {
-  StencilArgs a = base_args(c, M_CGF, dt == 0 ? 8 : 4);
+  StencilArgs a = cgf_args(c, dt);
   void* R[2] = {A.r, A.r2};
   void* Q[2] = {A.q, A.q2};
   a.in0 = R[k & 1];

@@ -79,6 +79,7 @@ struct StencilArgs {
   unsigned long long* status;  // CGF: host word that gets the progress after each launch (nullable)
   unsigned gen;                // CGF: tag of the solve in that word
   int first;                   // CG1, CGF: first iteration (p = r)
+  int shape;                   // CGF: tile shape
   int order;                   // tile order: 0 x-tiles fastest, 1 y-tiles fastest
   int nt_store;                // 1: outputs written with non-temporal stores
   RobinCorner rb;              // BC_ROBIN corner blocks

@@ -34,16 +34,13 @@ constexpr int kTileX = 64;
 constexpr int imin(int a, int b) { return a < b ? a : b; }
 constexpr int kLdsMax = 160 * 1024;  // LDS one workgroup may hold on gfx950
 
-// Rows per row wave of the one-kernel CG iteration: four in FP32, two in FP64.
-constexpr int cgf_rows_per_wave(int es) { return es == 4 ? 4 : 2; }
-
 // LDS of the one-kernel CG iteration (degree n, tile height ty, 64 columns, es-byte compute type):
 // staged plane (x halo of at most 8 columns a side: one 16-byte vector of bf16), the two x-pass
-// planes, the p and r rings, the reduction slots, and the Robin corner tables and z-accumulators
+// planes, the p and r rings, the reduction slots of up to 16 waves, and the Robin corner tables and z-accumulators
 // (one-element placeholders otherwise).  An upper bound of what the kernel declares (it asserts so).
 constexpr int cgf_lds_bytes(int n, int ty, int bc, int es) {
   return es * ((ty + 2 * n) * (64 + 16) + 2 * (ty + 2 * n) * 64 + (2 * n + 3) * ty * 64) +
-         8 * 4 * (ty / cgf_rows_per_wave(es)) +
+         8 * 4 * 16 +
          (bc == BC_ROBIN ? es * (4 * kRobinMaxZ * kRobinMaxZ + (2 * (n / 2) + 1) * ty * 64) : 2 * es);
 }
 
@@ -58,19 +55,42 @@ constexpr int cgf_tile_y(int n, int bc, int es) {
                  : (cgf_lds_bytes(n, 16, bc, 8) <= kLdsMax ? 16 : 8);
 }
 
+// Shapes of the one-kernel CG iteration.  Shape 0 is the tile above.  On smaller grids its few, large
+// workgroups leave CUs idle, and where every workgroup has a CU to itself the time per plane is the
+// instructions of one wave: shape 1 is 32 rows in FP32, and 8 in FP64 with one row per wave; shape 2 is 16
+// rows of two per wave in FP32.  The plan takes the cheapest (stencil_plan_zc).  Measured, cubic
+// periodic, us per iteration with shapes 0 / 1 / 2 in FP32: 32^3 25.5 / 22.7 / 19.5, 100^3 32.1 / 30.1 / 29.1,
+// 192^3 58.5 / 55.3 / 60.7, 256^3 131.8 / 124.0 / 146.1; with 0 / 1 in FP64: 32^3 22.2 / 19.2, 64^3 24.8 / 22.9,
+// 100^3 33.5 / 36.0.  Robin boxes and the bf16-stored direction have shape 0 only.
+constexpr int kCgfShapes = 3;
+// tile height of a shape, 0 if there is none
+constexpr int cgf_shape_ty(int shape, int n, int bc, int es) {
+  return shape == 0 ? cgf_tile_y(n, bc, es)
+                    : (bc == BC_ROBIN ? 0
+                                      : (es == 4 ? (shape == 2 ? 16 : (cgf_tile_y(n, bc, 4) > 32 ? 32 : 0))
+                                                 : (shape == 1 ? 8 : 0)));
+}
+constexpr int cgf_shape_rows_per_wave(int shape, int es) {
+  return es == 4 ? (shape == 2 ? 2 : 4) : (shape == 1 ? 1 : 2);
+}
+// A plane's time in a lone workgroup (us, cubic; between the value on an idle chip and on a busy one)
+constexpr double cgf_plane_time(int shape, int es) {
+  return es == 4 ? (shape == 0 ? 2.9 : (shape == 1 ? 2.25 : 1.65)) : (shape == 0 ? 2.3 : 1.65);
+}
+
 // Tile height per (mode, compute precision, degree, boundary): taller tiles re-read fewer halo
 // rows.  The FP64 kernels take 16 rows in eight row waves of two rows (the FP64 ring and column
-// windows of two rows leave room for more waves per SIMD than four rows in four waves).
-constexpr int stencil_tile_y(int mode, int compute_bytes, int n, int bc) {
-  return compute_bytes == 4
-             ? ((mode == M_APPLY) ? 32
-                                  : (mode == M_CG1 ? STENCIL_CG_TY : (mode == M_CGF ? cgf_tile_y(n, bc, 4) : 16)))
-             : ((mode == M_RESID || mode == M_RHSRES) ? STENCIL_RESID_TY : (mode == M_CGF ? cgf_tile_y(n, bc, 8) : 16));
+// windows of two rows leave room for more waves per SIMD than four rows in four waves).  shape: of
+// the one-kernel CG iteration.
+constexpr int stencil_tile_y(int mode, int compute_bytes, int n, int bc, int shape = 0) {
+  return mode == M_CGF ? cgf_shape_ty(shape, n, bc, compute_bytes)
+                       : (compute_bytes == 4 ? (mode == M_APPLY ? 32 : (mode == M_CG1 ? STENCIL_CG_TY : 16))
+                                             : ((mode == M_RESID || mode == M_RHSRES) ? STENCIL_RESID_TY : 16));
 }
-// Row waves per workgroup: four for the FP32 kernels, except the one-kernel CG iteration, whose
-// waves keep four rows each (two in FP64); eight for the other FP64 kernels.
-constexpr int stencil_tile_wy(int mode, int compute_bytes, int n, int bc) {
-  return mode == M_CGF ? stencil_tile_y(mode, compute_bytes, n, bc) / cgf_rows_per_wave(compute_bytes)
+// Row waves per workgroup: four for the FP32 kernels, except the one-kernel CG iteration; eight for the
+// other FP64 kernels.
+constexpr int stencil_tile_wy(int mode, int compute_bytes, int n, int bc, int shape = 0) {
+  return mode == M_CGF ? stencil_tile_y(mode, compute_bytes, n, bc, shape) / cgf_shape_rows_per_wave(shape, compute_bytes)
                        : ((mode == M_RESID || mode == M_RHSRES) ? STENCIL_RESID_WY
                                                                    : (compute_bytes == 8 ? STENCIL_F64_WY : 4));
 }
@@ -110,9 +130,12 @@ constexpr int stencil_min_waves(int mode, int compute_bytes, int n, int bc) {
 constexpr double stencil_latency_load(int mode, int compute_bytes) {
   return mode == M_CGF ? 1.0 : (compute_bytes == 4 ? 1.8 : ((mode == M_RESID || mode == M_RHSRES) ? 1.5 : 1.3));
 }
-int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail);
-// zchunk > 0: the caller's own chunk length
-int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk);
+int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail,
+            double* cost = nullptr);
+// zchunk > 0: the caller's own chunk length.  *shape (M_CGF): the shape the plan takes, the one with the
+// smallest cost times its time per plane (0 with a caller's chunk length).
+int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk,
+                    int* shape);
 
 // One stencil launch of degree N for a (mode, input, compute, output) type combination and
 // boundary condition BC; defined in stencil_kernel.h and instantiated per degree and boundary

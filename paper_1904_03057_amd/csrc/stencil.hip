@@ -24,14 +24,15 @@ static hipError_t launch_n(const StencilArgs& a, int n, int bc, hipStream_t st) 
 }
 
 int stencil_blocks(const StencilArgs& a, int mode, int compute_bytes, int n, int bc) {
-  const int ty = stencil_tile_y(mode, compute_bytes, n, bc);
+  const int ty = stencil_tile_y(mode, compute_bytes, n, bc, a.shape);
   const int wx = (mode == M_APPLY && compute_bytes == 4) ? STENCIL_APPLY_WX : 1;
   return ((a.nx + 64 * wx - 1) / (64 * wx)) * ((a.ny + ty - 1) / ty) * a.nchunks;
 }
 
 // The planes per chunk with the smallest (zc + halo) max(lat, load), load the workgroups of the busiest of
 // `slots` equal processors; at most most_blocks workgroups, or one chunk.
-int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail) {
+int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail,
+            double* least) {
   const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(1, most_blocks / tiles));
   int64_t best = nz;
   double cost = 0.0;
@@ -44,21 +45,37 @@ int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks,
       best = zc;
     }
   }
+  if (least) *least = cost;
   return (int)best;
 }
 
-int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk) {
+int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk,
+                    int* shape) {
+  if (shape) *shape = 0;
   if (zchunk > 0) return (int)std::min<int64_t>(zchunk, nz);
-  const int ty = stencil_tile_y(mode, compute_bytes, n, bc);
   const int wx = (mode == M_APPLY && compute_bytes == 4) ? STENCIL_APPLY_WX : 1;
-  const int64_t tiles = ((nx + 64 * wx - 1) / (64 * wx)) * ((ny + ty - 1) / ty);
+  const int64_t tiles_x = (nx + 64 * wx - 1) / (64 * wx);
   if (compute_bytes == 8 && (mode == M_CGF || mode == M_CG1) && bc == BC_ROBIN && n >= 2) {
     const int64_t plan_tiles = ((nx + 63) / 64) * ((ny + 15) / 16);
     const int64_t chunks = std::max<int64_t>(1, std::min((8192 + plan_tiles - 1) / plan_tiles, nz / (4 * (2 * n + 1))));
     return (int)((nz + chunks - 1) / chunks);
   }
-  return plan_zc(tiles, nz, 2 * n, 256, 16384, stencil_latency_load(mode, compute_bytes),
-                 mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75);
+  int zc = 0;
+  double least = 0.0;
+  for (int sh = 0; sh < (mode == M_CGF && shape ? kCgfShapes : 1); ++sh) {
+    const int ty = stencil_tile_y(mode, compute_bytes, n, bc, sh);
+    if (ty == 0) continue;
+    double cost;
+    const int z = plan_zc(tiles_x * ((ny + ty - 1) / ty), nz, 2 * n, 256, 16384, stencil_latency_load(mode, compute_bytes),
+                          mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75, &cost);
+    cost *= cgf_plane_time(sh, compute_bytes);
+    if (zc == 0 || cost < least) {
+      zc = z;
+      least = cost;
+      if (shape) *shape = sh;
+    }
+  }
+  return zc;
 }
 
 // dtype codes: 0 = f64, 1 = f32, 2 = bf16

@@ -641,25 +641,17 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
 // host-side launch helpers
 
 // Tile shape per (degree, mode, compute type, boundary): heights and row waves from stencil.h (the
-// host sizes the partial-sum buffers by stencil_blocks); the FP32 apply may take WX column
-// groups (STENCIL_APPLY_WX, one by default).
-template <int N, int MODE, typename Tc, int BC> constexpr int tile_y() {
-  return stencil_tile_y(MODE, (int)sizeof(Tc), N, BC);
-}
-template <int N, int MODE, typename Tc, int BC> constexpr int tile_wy() {
-  return stencil_tile_wy(MODE, (int)sizeof(Tc), N, BC);
-}
+// host sizes the partial-sum buffers by stencil_blocks); the FP32 apply may take WX column groups
+// (STENCIL_APPLY_WX, one by default).
 template <int MODE, typename Tc> constexpr int tile_wx() {
   return (MODE == M_APPLY && sizeof(Tc) == 4) ? STENCIL_APPLY_WX : 1;
 }
 
-// One launch for boundary condition BC (one object per degree and boundary condition, so the
-// instances compile in parallel; stencil.h dispatches on the run-time boundary condition).
-template <int N, int MODE, typename Tin, typename Tc, typename Tout, int BC>
-hipError_t launch_bcx(const StencilArgs& a0, bool vec, hipStream_t st) {
-  constexpr int TY = tile_y<N, MODE, Tc, BC>();
+template <int N, int MODE, typename Tin, typename Tc, typename Tout, int BC, int SHAPE>
+hipError_t launch_shape(const StencilArgs& a0, bool vec, hipStream_t st) {
+  constexpr int TY = stencil_tile_y(MODE, (int)sizeof(Tc), N, BC, SHAPE);
   constexpr int WX = tile_wx<MODE, Tc>();
-  constexpr int WY = tile_wy<N, MODE, Tc, BC>();
+  constexpr int WY = stencil_tile_wy(MODE, (int)sizeof(Tc), N, BC, SHAPE);
   StencilArgs a = a0;  // geometry for this tile shape
   a.tiles_x = (a.nx + 64 * WX - 1) / (64 * WX);
   a.tiles_y = (a.ny + TY - 1) / TY;
@@ -670,6 +662,20 @@ hipError_t launch_bcx(const StencilArgs& a0, bool vec, hipStream_t st) {
   else
     hipLaunchKernelGGL((stencil_kernel<N, TY, MODE, Tin, Tc, Tout, BC, false, WX, WY>), grid, block, 0, st, a);
   return hipGetLastError();
+}
+
+// One launch for boundary condition BC (one object per degree and boundary condition, so the
+// instances compile in parallel; stencil.h dispatches on the run-time boundary condition).
+template <int N, int MODE, typename Tin, typename Tc, typename Tout, int BC>
+hipError_t launch_bcx(const StencilArgs& a, bool vec, hipStream_t st) {
+  if constexpr (MODE == M_CGF && sizeof(Tin) == sizeof(Tc)) {
+    if constexpr (cgf_shape_ty(1, N, BC, (int)sizeof(Tc)) > 0)
+      if (a.shape == 1) return launch_shape<N, MODE, Tin, Tc, Tout, BC, 1>(a, vec, st);
+    if constexpr (cgf_shape_ty(2, N, BC, (int)sizeof(Tc)) > 0)
+      if (a.shape == 2) return launch_shape<N, MODE, Tin, Tc, Tout, BC, 2>(a, vec, st);
+  }
+  if (a.shape != 0) return hipErrorInvalidValue;
+  return launch_shape<N, MODE, Tin, Tc, Tout, BC, 0>(a, vec, st);
 }
 
 // The fused rhs and residual for degree N and boundary BC (no Robin instance: the caller falls back
