@@ -58,7 +58,7 @@ __device__ __forceinline__ float gelu_f(float x) {
   p = fmaf(p, t, 1.414555073e+00f);
   p = fmaf(p, t, -3.213009119e+00f);
   const float q = t * __builtin_amdgcn_exp2f(fmaf(y * y, -0.72134752044448170f, p));  // Phi(-y)
-  return fmaf(-y, q, fmaxf(x, 0.f));
+  return fmaf(-y, q, __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff()));  // max(x, 0) in one instruction
 }
 __device__ __forceinline__ float gelu_grad_f(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
@@ -72,7 +72,7 @@ struct Grid3 {
 // ------------------------------------------------------------------------------------------
 // convolution on the matrix cores
 
-enum Epi { EPI_GELU = 0, EPI_LINEAR = 1, EPI_BWD = 2, EPI_RAW = 3 };
+enum Epi { EPI_GELU = 0, EPI_LINEAR = 1, EPI_BWD = 2, EPI_RAW = 3, EPI_GELU_Z = 4 };
 
 // Geometry of the z-marching convolution: a workgroup owns a 32 x 8 column of output voxels and
 // marches through a chunk of zc planes, keeping the three input planes a output plane needs in an
@@ -116,7 +116,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 // in: [voxel][CIS] bf16; wpk: packed A operands [steps][64 lanes][8]; out per epilogue:
-//   EPI_GELU:   zout (f32 [voxel][16], nullable) = acc + bias; yout (bf16 [voxel][16]) = GELU(z)
+//   EPI_GELU:   yout (bf16 [voxel][16]) = GELU(z), z = acc + bias
+//   EPI_GELU_Z: as EPI_GELU, and zout (f32 [voxel][16]) = z
 //   EPI_LINEAR: fout (f32 [voxel]) = (acc[0] + bias[0]) * (*scale)          (last layer, 1 channel)
 //   EPI_BWD:    yout (bf16 [voxel][16]) = acc * GELU'(zprev[voxel][c])       (backward data)
 //   EPI_RAW:    fout (f32 [voxel][COS]) = acc (+ bias if bias != NULL)       (parity probes)
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
   const int bx = bid % geo.tx, by = (bid / geo.tx) % geo.ty, ch = bid / (geo.tx * geo.ty);
   const int x0 = bx * CTX, y0 = by * CTY, z0 = ch * geo.zc;
   const int zc = min(geo.zc, g.nz - z0);
+  const bool inside = x0 + CTX <= g.nx && y0 + CTY <= g.ny;
 
   // A operands (weights) for all K-steps, loaded once and kept in registers
   bf16x8 wa[STEPS];
@@ -287,36 +289,43 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
             }
           }
         }
-#pragma unroll
-        for (int r = 0; r < WROWS; ++r) {
-          // D layout: acc[r] = Out[channel 4 grp + r][voxel vx]
+        // D layout: acc[r] = Out[channel 4 grp + r][voxel vx]
+        auto emit = [&](int r) {
           const f32x4 A = acc[r];
           const int gx = x0 + xh * 16 + vx, gy = y0 + yb + r;
-          if (gx < g.nx && gy < g.ny) {
-            const int64_t vi = (int64_t)gz * plane + (int64_t)gy * g.nx + gx;
-            if (EPI == EPI_GELU) {
-              float z[4];
+          const int64_t vi = (int64_t)gz * plane + (int64_t)gy * g.nx + gx;
+          if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_Z) {
+            float z[4];
 #pragma unroll
-              for (int c = 0; c < 4; ++c) z[c] = A[c] + bz[c];
-              if (zout) *(float4*)(zout + vi * 16 + c0) = make_float4(z[0], z[1], z[2], z[3]);
-              uint2 packed;
-              packed.x = pack_bf16x2(gelu_f(z[0]), gelu_f(z[1]));
-              packed.y = pack_bf16x2(gelu_f(z[2]), gelu_f(z[3]));
-              *(uint2*)(yout + vi * 16 + c0) = packed;
-            } else if (EPI == EPI_LINEAR) {
-              if (grp == 0) fout[vi] = (float)(((double)A[0] + (double)bz[0]) * scale[0]);
-            } else if (EPI == EPI_BWD) {
-              const float4 zp = *(const float4*)(zprev + vi * 16 + c0);
-              uint2 packed;
-              packed.x = pack_bf16x2(A[0] * gelu_grad_f(zp.x), A[1] * gelu_grad_f(zp.y));
-              packed.y = pack_bf16x2(A[2] * gelu_grad_f(zp.z), A[3] * gelu_grad_f(zp.w));
-              *(uint2*)(yout + vi * 16 + c0) = packed;
-            } else {
+            for (int c = 0; c < 4; ++c) z[c] = A[c] + bz[c];
+            if (EPI == EPI_GELU_Z) *(float4*)(zout + vi * 16 + c0) = make_float4(z[0], z[1], z[2], z[3]);
+            uint2 packed;
+            packed.x = pack_bf16x2(gelu_f(z[0]), gelu_f(z[1]));
+            packed.y = pack_bf16x2(gelu_f(z[2]), gelu_f(z[3]));
+            *(uint2*)(yout + vi * 16 + c0) = packed;
+          } else if (EPI == EPI_LINEAR) {
+            if (grp == 0) fout[vi] = (float)(((double)A[0] + (double)bz[0]) * scale[0]);
+          } else if (EPI == EPI_BWD) {
+            const float4 zp = *(const float4*)(zprev + vi * 16 + c0);
+            uint2 packed;
+            packed.x = pack_bf16x2(A[0] * gelu_grad_f(zp.x), A[1] * gelu_grad_f(zp.y));
+            packed.y = pack_bf16x2(A[2] * gelu_grad_f(zp.z), A[3] * gelu_grad_f(zp.w));
+            *(uint2*)(yout + vi * 16 + c0) = packed;
+          } else {
 #pragma unroll
-              for (int c = 0; c < 4; ++c)
-                if (c0 + c < COS) fout[vi * COS + c0 + c] = A[c] + bz[c];
-            }
+            for (int c = 0; c < 4; ++c)
+              if (c0 + c < COS) fout[vi * COS + c0 + c] = A[c] + bz[c];
           }
+        };
+        // a tile inside the grid has no lane to mask: its four rows' epilogues form one block of
+        // instructions, in which the long chains of the activation overlap
+        if (inside) {
+#pragma unroll
+          for (int r = 0; r < WROWS; ++r) emit(r);
+        } else {
+#pragma unroll
+          for (int r = 0; r < WROWS; ++r)
+            if (x0 + xh * 16 + vx < g.nx && y0 + yb + r < g.ny) emit(r);
         }
         __syncthreads();  // every wave is done with slot ph (plane z0 + i - 1)
         if (i + 3 <= zc + 1) {
@@ -956,43 +965,42 @@ static int conv_blocks(const int64_t grid[3]) {
   return c.tx * c.ty * c.nch;
 }
 
-static int smooth(tbs_net* n, float* buf, float* tmp, Grid3 g);
+static int smooth(tbs_net* n, const float* src, float* tmp, float* dst, Grid3 g);
 
 // forward of one sample; x0 already prepared.  keep = training (store z and all y, and leave the
-// network output unscaled for the loss); otherwise the output is the guess du = o * sc[2].
-static int forward_layers(tbs_net* n, Grid3 g, int keep) {
+// network output unscaled for the loss); otherwise the output is the guess du = o * sc[2].  It goes to
+// `out` (w.o or the caller's array).
+static int forward_layers(tbs_net* n, Grid3 g, int keep, float* out) {
   const int64_t grid[3] = {g.nx, g.ny, g.nz};
   const int nb = conv_blocks(grid);
   NetWs& w = n->w;
-  uint16_t* y0 = keep ? w.y[0] : w.y[0];
-  uint16_t* y1 = keep ? w.y[1] : w.y[1];
   uint16_t* y2 = keep ? w.y[2] : w.y[0];
-  hipLaunchKernelGGL((conv_mfma<2, 16, EPI_GELU>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.x0, w.wf,
-                     w.bias, g, keep ? w.z[0] : nullptr, y0, nullptr, nullptr, nullptr);
-  hipLaunchKernelGGL((conv_mfma<16, 16, EPI_GELU>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)y0,
-                     w.wf + PACK, w.bias + 16, g, keep ? w.z[1] : nullptr, y1, nullptr, nullptr, nullptr);
-  hipLaunchKernelGGL((conv_mfma<16, 16, EPI_GELU>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)y1,
-                     w.wf + 2 * PACK, w.bias + 32, g, keep ? w.z[2] : nullptr, y2, nullptr, nullptr, nullptr);
+#define GELU_LAYER(CI, IN, L, Y)                                                                                       \
+  if (keep)                                                                                                            \
+    hipLaunchKernelGGL((conv_mfma<CI, 16, EPI_GELU_Z>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)(IN),          \
+                       w.wf + (L) * PACK, w.bias + 16 * (L), g, w.z[L], Y, nullptr, nullptr, nullptr);                 \
+  else                                                                                                                 \
+    hipLaunchKernelGGL((conv_mfma<CI, 16, EPI_GELU>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)(IN),            \
+                       w.wf + (L) * PACK, w.bias + 16 * (L), g, nullptr, Y, nullptr, nullptr, nullptr)
+  GELU_LAYER(2, w.x0, 0, w.y[0]);
+  GELU_LAYER(16, w.y[0], 1, w.y[1]);
+  GELU_LAYER(16, w.y[1], 2, y2);
+#undef GELU_LAYER
   hipLaunchKernelGGL((conv_mfma<16, 1, EPI_LINEAR>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)y2,
                      w.wf + 3 * PACK, w.bias + 48, g, nullptr, nullptr, w.o, nullptr,
                      (const double*)(w.sc + (keep ? 3 : 2)));
   NCHK(hipGetLastError());
   // output low-pass (linear, so it commutes with the output scale); scratch: a free activation buffer
-  return smooth(n, w.o, keep ? (float*)w.gz[0] : (float*)w.y[1], g);
+  return smooth(n, w.o, keep ? (float*)w.gz[0] : (float*)w.y[1], out, g);
 }
 
-// buf <- B^SMOOTH_PASSES buf with B = Bx By Bz the binomial low-pass; tmp is scratch of N floats
-static int smooth(tbs_net* n, float* buf, float* tmp, Grid3 g) {
-  const int64_t N = (int64_t)g.nx * g.ny * g.nz;
+// dst <- B^2 src with B = Bx By Bz the binomial low-pass; tmp is scratch of N floats, dst may be src
+static int smooth(tbs_net* n, const float* src, float* tmp, float* dst, Grid3 g) {
+  static_assert(SMOOTH_PASSES == 2, "through tmp");
   const int zc = smooth_zchunk(g);
   const int sblocks = ((g.nx + SMX - 1) / SMX) * ((g.ny + SMY - 1) / SMY) * ((g.nz + zc - 1) / zc);
-  float* a = buf;
-  float* b = tmp;
-  for (int p = 0; p < SMOOTH_PASSES; ++p) {
-    hipLaunchKernelGGL(smooth3, dim3(sblocks), dim3(256), 0, n->st, (const float*)a, b, g, zc);
-    float* t = a; a = b; b = t;
-  }
-  if (a != buf) NCHK(hipMemcpyAsync(buf, a, (size_t)N * 4, hipMemcpyDeviceToDevice, n->st));
+  hipLaunchKernelGGL(smooth3, dim3(sblocks), dim3(256), 0, n->st, src, tmp, g, zc);
+  hipLaunchKernelGGL(smooth3, dim3(sblocks), dim3(256), 0, n->st, (const float*)tmp, dst, g, zc);
   NCHK(hipGetLastError());
   return TBS_OK;
 }
@@ -1020,10 +1028,7 @@ extern "C" int tbs_net_forward(tbs_net* n, const void* u, const void* q, int dty
   rc = dtype == TBS_F64 ? prepare(n, (const double*)u, (const double*)q, N, tau, n->out_scale)
                         : prepare(n, (const float*)u, (const float*)q, N, tau, n->out_scale);
   if (rc) return rc;
-  rc = forward_layers(n, g, 0);
-  if (rc) return rc;
-  if (du != n->w.o) NCHK(hipMemcpyAsync(du, n->w.o, (size_t)N * 4, hipMemcpyDeviceToDevice, n->st));
-  return TBS_OK;
+  return forward_layers(n, g, 0, du);
 }
 
 int tbs_net_guess_internal(tbs_net* n, const int64_t grid[3], int periodic, double tau, hipStream_t st,
@@ -1036,7 +1041,7 @@ int tbs_net_guess_internal(tbs_net* n, const int64_t grid[3], int periodic, doub
   Grid3 g{(int)grid[0], (int)grid[1], (int)grid[2], periodic ? 1 : 0};
   rc = prepare(n, u_prev, q, N, tau, n->out_scale);
   if (rc) return rc;
-  rc = forward_layers(n, g, 0);
+  rc = forward_layers(n, g, 0, n->w.o);
   if (rc) return rc;
   *du_out = n->w.o;
   return TBS_OK;
@@ -1061,12 +1066,12 @@ extern "C" int tbs_net_train_step(tbs_net* n, const float* u, const float* q, co
     const float* tb = du_t + (size_t)b * N;
     rc = prepare(n, ub, qb, N, tau, n->out_scale);
     if (rc) return rc;
-    rc = forward_layers(n, g, 1);
+    rc = forward_layers(n, g, 1, w.o);
     if (rc) return rc;
     float* gtmp = (float*)w.gz[0];
     hipLaunchKernelGGL(mse_grad, dim3(kRedBlocks), dim3(256), 0, n->st, (const float*)w.o, tb, N,
                        (const double*)w.sc, inv_total, gtmp, w.red);
-    rc = smooth(n, gtmp, (float*)w.gz[1], g);  // adjoint of the output filter (it is symmetric)
+    rc = smooth(n, gtmp, (float*)w.gz[1], gtmp, g);  // adjoint of the output filter (it is symmetric)
     if (rc) return rc;
     hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(2048), dim3(256), 0, n->st, (const float*)gtmp, w.gout, N);
     hipLaunchKernelGGL(loss_final, dim3(1), dim3(64), 0, n->st, (const double*)w.red, kRedBlocks, inv_total,
