@@ -160,6 +160,7 @@ struct tbs_ctx {
   // the one-kernel CG iteration: z-chunk and tile shape in FP32 and FP64 (a bf16-stored direction takes
   // shape 0 and zc[M_CGF])
   int cgf_zc[2], cgf_shape[2];
+  int dots_zc;  // > 0: FP64 iterations leave their sums to a second launch with this z-chunk (Robin boxes)
   int nparts;               // partial sums of the largest launch
   char* ws;
   size_t ws_bytes;
@@ -206,7 +207,20 @@ static void plan_geometry(tbs_ctx* c, int zchunk) {
         c->nparts = std::max(c->nparts, stencil_blocks(base_args(c, mode, es), mode, es, c->n, c->bc));
     }
     c->cgf_zc[f64] = stencil_plan_zc(c->nx, c->ny, c->nz, M_CGF, es, c->n, c->bc, zchunk, &c->cgf_shape[f64]);
+    if (f64) {
+      c->dots_zc = 0;
+      if (c->bc == TBS_BC_ROBIN && c->n >= 2 && zchunk == 0) {
+        const int dz = robin_dots_zc(c->nx, c->ny, c->nz, c->n);
+        if (robin_dots_apart(c->nx, c->ny, c->nz, c->n, c->cgf_zc[1])) c->dots_zc = dz;
+        else c->cgf_zc[1] = dz;
+      }
+    }
     c->nparts = std::max(c->nparts, stencil_blocks(cgf_args(c, f64 ? 0 : 1), M_CGF, es, c->n, c->bc));
+  }
+  if (c->dots_zc) {
+    StencilArgs a = cgf_args(c, 0);
+    a.nchunks = (int)((c->nz + c->dots_zc - 1) / c->dots_zc);
+    c->nparts = std::max(c->nparts, stencil_blocks(a, M_CGF, 8, c->n, c->bc));
   }
 }
 
@@ -844,8 +858,22 @@ static int cgf_async(tbs_ctx* c, const CgArrays& A, int dt, int k, bool publish)
   c->cgf_pend = (pend == 2 ? 0 : pend) + 1;
   if (pend == 2) c->cgf_xzero = false;
   int ps = prof_begin(c, dt == 0 ? 15 : (dt == 1 ? 11 : 12), k, b1);
+  const bool apart = dt == 0 && c->dots_zc > 0;
+  StencilArgs d = a;
+  if (apart) {
+    a.part0 = nullptr;
+    a.status = nullptr;
+  }
   HIPCHK(launch_cgf(a, c->n, c->bc, dt, c->st));
   prof_end(c, ps);
+  if (apart) {
+    d.in0 = a.out2;
+    d.in1 = a.out1;
+    d.in2 = a.out0;
+    d.zc = c->dots_zc;
+    d.nchunks = (int)((c->nz + d.zc - 1) / d.zc);
+    HIPCHK(launch_cg_dots(d, c->n, c->st));
+  }
   return TBS_OK;
 }
 

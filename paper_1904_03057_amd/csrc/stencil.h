@@ -119,19 +119,20 @@ constexpr int stencil_min_waves(int mode, int compute_bytes, int n, int bc) {
 // replaces the ceiling (which took four chunks for the FP32 apply at 928^3: 1.81 against 1.72 ms); 0.75,
 // or 1.5 for the FP32 apply, which is bound by its arithmetic and not by the halo planes' traffic (with
 // 1.5 for all, twelve chunks instead of eight, the FP32 CG step at 928^3 took 292 against 280 ms).
-// FP64 CG on a Robin box of degree 2 or more keeps chunks of at least 4 (2n+1) planes: its nearly empty
-// corner functions take hundreds to thousands of iterations, and sums grouped in another way moved
-// its solutions by up to 4e-8 of their RMS.  The latency
-// loads are the measured ratios of a lone workgroup's time per plane to the added time of one more
-// on the same CU.  Measured (cubic, us per launch, against chunks of at least 4 (2n+1) planes and
-// about 8192 workgroups for every kernel): FP64 CG iteration 67 -> 18 at 32^3, 78 -> 36 at 128^3, 262 ->
-// 198 at 256^3; FP32 CG iteration 93 -> 24 at 64^3, 102 -> 55 at 192^3; FP32 apply 75 -> 20 at 100^3, 79 ->
-// 52 at 256^3; the model's ratios hold within 5 % up to 400^3.
 constexpr double stencil_latency_load(int mode, int compute_bytes) {
   return mode == M_CGF ? 1.0 : (compute_bytes == 4 ? 1.8 : ((mode == M_RESID || mode == M_RHSRES) ? 1.5 : 1.3));
 }
 int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail,
             double* cost = nullptr);
+// FP64 CG on a Robin box of degree 2 or more: its nearly empty corner functions take hundreds to thousands
+// of iterations, and sums grouped in another way moved its solutions by up to 4e-8 of their RMS.  So its
+// sums keep the grouping of chunks of at least 4 (2n+1) planes (about 8192 workgroups).  Where the plan's own
+// chunks are faster by more than kRobinDotsGain, the iteration runs with those and leaves the sums to a
+// second launch that adds them in that grouping (cg_dots_kernel, which reads r, p and q again): cubic
+// 121x104x90, 36 + 22 us per iteration against 105 with the long chunks.
+constexpr double kRobinDotsGain = 1.7;
+int robin_dots_zc(int64_t nx, int64_t ny, int64_t nz, int n);
+bool robin_dots_apart(int64_t nx, int64_t ny, int64_t nz, int n, int zc);
 // zchunk > 0: the caller's own chunk length.  *shape (M_CGF): the shape the plan takes, the one with the
 // smallest cost times its time per plane (0 with a caller's chunk length).
 int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_bytes, int n, int bc, int zchunk,
@@ -162,6 +163,8 @@ hipError_t launch_rhs(const StencilArgs& a, int n, int bc, int dt, hipStream_t s
 hipError_t launch_cg1(const StencilArgs& a, int n, int bc, int dt, hipStream_t st);
 // CGF (one-kernel CG iteration): dt = 1 (all f32), 2 (f32 with p stored as bf16)
 hipError_t launch_cgf(const StencilArgs& a, int n, int bc, int dt, hipStream_t st);
+// the sums of a Robin FP64 CGF launch that was given no partial-sum arrays (in0 = r, in1 = p, in2 = q)
+hipError_t launch_cg_dots(const StencilArgs& a, int n, hipStream_t st);
 hipError_t launch_resid(const StencilArgs& a, int n, int bc, int r_dt, hipStream_t st);
 // RHSRES: u (f64, in0) -> b = M u (f64, out1) and r = (b - A u) rscale (f32, out0), with the partial
 // sums of r.r and (b rscale).(b rscale); periodic and Dirichlet only (hipErrorInvalidValue on Robin)
