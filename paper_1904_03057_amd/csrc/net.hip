@@ -60,8 +60,23 @@ __device__ __forceinline__ float gelu_f(float x) {
   const float q = t * __builtin_amdgcn_exp2f(fmaf(y * y, -0.72134752044448170f, p));  // Phi(-y)
   return fmaf(-y, q, __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff()));  // max(x, 0) in one instruction
 }
+// GELU'(x) = Phi(x) + x phi(x) from the tail's side: GELU'(-y) = e (0.5 + y (t P(t) - 1 / sqrt(2 pi))),
+// e = 2^(-y^2 / (2 ln 2)), t = 1 / (1 + y / 4), and GELU'(y) = 1 - GELU'(-y).  P of degree 6 fitted by
+// fit_gelu.py; every rounding but the last is scaled by e or y: error against 64 bits at most 1.11e-7, rms
+// 2.2e-8 on [-8, 8] (1.44e-7 and 2.6e-8 with erff and expf, at three times the instructions).
 __device__ __forceinline__ float gelu_grad_f(float x) {
-  return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
+  const float y = fabsf(x);
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.25f, y, 1.0f));
+  float p = 2.358977310e-02f;
+  p = fmaf(p, t, -6.521388888e-02f);
+  p = fmaf(p, t, 8.545549586e-03f);
+  p = fmaf(p, t, -6.954040378e-02f);
+  p = fmaf(p, t, -7.072117180e-02f);
+  p = fmaf(p, t, -1.006303057e-01f);
+  p = fmaf(p, t, -1.249715537e-01f);
+  const float e = __builtin_amdgcn_exp2f(y * y * -0.72134752044448170f);
+  const float d = fmaf(y, fmaf(t, p, -0.39894228040143268f), 0.5f);
+  return fmaf(x > 0.f ? -e : e, d, x > 0.f ? 1.0f : 0.0f);
 }
 
 struct Grid3 {
@@ -121,23 +136,27 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 //   EPI_LINEAR: fout (f32 [voxel]) = (acc[0] + bias[0]) * (*scale)          (last layer, 1 channel)
 //   EPI_BWD:    yout (bf16 [voxel][16]) = acc * GELU'(zprev[voxel][c])       (backward data)
 //   EPI_RAW:    fout (f32 [voxel][COS]) = acc (+ bias if bias != NULL)       (parity probes)
-// Two K layouts: with 16 (or zero-padded 1) input channels each K-step holds 2 taps x 16
-// channels (15 steps, order tap16); with 2 input channels it holds 16 taps x 2 channels (2 steps,
-// 27 taps padded to 32), and the ring keeps only the 2 channels.  Each wave owns 4 consecutive
+// Two K layouts: with 16 input channels each K-step holds 2 taps x 16 channels (15 steps, order
+// tap16); with 2 (or 1) input channels it holds 16 taps x 2 (32 taps x 1) channels (2 steps or one,
+// 27 taps padded to 32), and the ring keeps only those channels.  Each wave owns 4 consecutive
 // rows (y) of 16 voxels (x) per plane; the plane loop is unrolled by the ring period so all LDS
 // reads of the B operands use immediate offsets.
+//
+// The backward data pass moves 96 (1 -> 16 channels) or 128 bytes per voxel, 42 or 56 us at 128^3 at the
+// copy rate, and takes 53 or 68 us there; 88 or 83 us with 1 channel padded to 16, GELU' from erff and expf
+// and z loaded only after the products.
 template <int CIS, int COS, int EPI>
 __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
                                                  const float* __restrict__ bias, Grid3 g,
                                                  float* __restrict__ zout, uint16_t* __restrict__ yout,
                                                  float* __restrict__ fout, const float* __restrict__ zprev,
                                                  const double* __restrict__ scale) {
-  constexpr bool TWO = (CIS == 2);
-  constexpr int STEPS = TWO ? 2 : NSTEP;
-  constexpr int VW = TWO ? 2 : 16;                  // bf16 per staged voxel
+  constexpr bool TAPS = (CIS < 16);                 // K runs over taps x CIS channels
+  constexpr int STEPS = TAPS ? CIS : NSTEP;
+  constexpr int VW = CIS;                           // bf16 per staged voxel
   constexpr int UNITS = CIS == 16 ? 2 * PLV : PLV;  // load units per plane (16 B, or one voxel)
   constexpr int UPT = (UNITS + 255) / 256;          // units per thread
-  using Unit = typename std::conditional<CIS == 16, uint4, typename std::conditional<TWO, uint32_t, uint16_t>::type>::type;
+  using Unit = typename std::conditional<CIS == 16, uint4, typename std::conditional<CIS == 2, uint32_t, uint16_t>::type>::type;
   __shared__ __attribute__((aligned(16))) uint16_t st[3 * PLV * VW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const ConvGeo geo = conv_geo(g);
@@ -177,10 +196,6 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
     }
     uoff[q] = ok ? gy * g.nx + gx : -1;
   }
-  if (CIS == 1) {  // channels 1..15 of the ring stay zero
-    for (int i = tid; i < 3 * PLV * VW / 8; i += 256) ((uint4*)st)[i] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-  }
   Unit pre[UPT];
   // fetch relative plane j (global plane z0 - 1 + j) into pre
   auto fetch = [&](int j) {
@@ -194,7 +209,7 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
       pre[q] = Unit{};
       if (pv && uoff[q] >= 0) {
         if constexpr (CIS == 16) pre[q] = ((const uint4*)(in + (pb + uoff[q]) * 16))[(tid + 256 * q) & 1];
-        else if constexpr (TWO) pre[q] = *(const uint32_t*)(in + (pb + uoff[q]) * 2);
+        else if constexpr (CIS == 2) pre[q] = *(const uint32_t*)(in + (pb + uoff[q]) * 2);
         else pre[q] = in[pb + uoff[q]];
       }
     }
@@ -205,8 +220,7 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
       const int u = tid + 256 * q;
       if (UNITS % 256 == 0 || u < UNITS) {
         if constexpr (CIS == 16) ((uint4*)st)[slot * PLV * 2 + u] = pre[q];
-        else if constexpr (TWO) ((uint32_t*)st)[slot * PLV + u] = pre[q];
-        else st[(slot * PLV + u) * 16] = pre[q];
+        else ((Unit*)st)[slot * PLV + u] = pre[q];
       }
     }
   };
@@ -215,18 +229,19 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
   // y = 4 (w >> 1) + r (r = 0..3) of x half w & 1
   const int yb = 4 * (wave >> 1), xh = wave & 1;
   const int lb = yb * SX + xh * 16 + vx;
-  int loff[TWO ? 24 : 5];
-  if (TWO) {
-    // k = 8 grp + j: tap 16 s + 4 grp + j/2, channel j % 2; padding taps (> 26) read tap 13
+  constexpr int TPL = 8 / (TAPS ? CIS : 8);  // taps of a lane per K-step
+  int loff[TAPS ? 24 : 5];
+  if (TAPS) {
+    // k = 8 grp + j: tap (32 s + 8 grp + j) / CIS, channel j % CIS; padding taps (> 26) read tap 13
 #pragma unroll
     for (int ph = 0; ph < 3; ++ph)
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int s = 0; s < STEPS; ++s)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          int tap = 16 * s + 4 * grp + t;
+        for (int t = 0; t < TPL; ++t) {
+          int tap = (4 * s + grp) * TPL + t;
           if (tap > 26) tap = 13;
-          loff[8 * ph + 4 * s + t] = (lb + ((ph + tap / 9) % 3) * PLV + ((tap / 3) % 3) * SX + tap % 3) * 2;
+          loff[8 * ph + TPL * s + t] = (lb + ((ph + tap / 9) % 3) * PLV + ((tap / 3) % 3) * SX + tap % 3) * CIS;
         }
   } else {
     // k = 8 grp + j: tap tap16(s, grp >> 1), channel 8 (grp & 1) + j
@@ -255,14 +270,21 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
         f32x4 acc[WROWS];
 #pragma unroll
         for (int r = 0; r < WROWS; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (TWO) {
+        float4 zp[EPI == EPI_BWD ? WROWS : 1];  // in flight during the products (lanes outside: the last voxel)
+        if constexpr (EPI == EPI_BWD)
+#pragma unroll
+          for (int r = 0; r < WROWS; ++r) {
+            const int gx = min(x0 + xh * 16 + vx, g.nx - 1), gy = min(y0 + yb + r, g.ny - 1);
+            zp[r] = *(const float4*)(zprev + ((int64_t)gz * plane + (int64_t)gy * g.nx + gx) * 16 + c0);
+          }
+        if constexpr (TAPS) {
 #pragma unroll
           for (int r = 0; r < WROWS; ++r)
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
-              uint32_t w4[4];
+              Unit w4[TPL];
 #pragma unroll
-              for (int t = 0; t < 4; ++t) w4[t] = *(const uint32_t*)(st + loff[8 * ph + 4 * s + t] + r * SX * 2);
+              for (int t = 0; t < TPL; ++t) w4[t] = *(const Unit*)(st + loff[8 * ph + TPL * s + t] + r * SX * CIS);
               bf16x8 bv;
               __builtin_memcpy(&bv, w4, 16);
               acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[s], bv, acc[r], 0, 0, 0);
@@ -306,10 +328,9 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
           } else if (EPI == EPI_LINEAR) {
             if (grp == 0) fout[vi] = (float)(((double)A[0] + (double)bz[0]) * scale[0]);
           } else if (EPI == EPI_BWD) {
-            const float4 zp = *(const float4*)(zprev + vi * 16 + c0);
             uint2 packed;
-            packed.x = pack_bf16x2(A[0] * gelu_grad_f(zp.x), A[1] * gelu_grad_f(zp.y));
-            packed.y = pack_bf16x2(A[2] * gelu_grad_f(zp.z), A[3] * gelu_grad_f(zp.w));
+            packed.x = pack_bf16x2(A[0] * gelu_grad_f(zp[r].x), A[1] * gelu_grad_f(zp[r].y));
+            packed.y = pack_bf16x2(A[2] * gelu_grad_f(zp[r].z), A[3] * gelu_grad_f(zp[r].w));
             *(uint2*)(yout + vi * 16 + c0) = packed;
           } else {
 #pragma unroll
@@ -752,10 +773,11 @@ __global__ __launch_bounds__(64) void pack_weights(const float* __restrict__ w, 
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     float val = 0.f;
-    if (!flip && ci_n == 2) {
-      // two-channel layout: k = 8 grp + j -> tap 16 s + 4 grp + j/2, channel j % 2 (2 steps)
-      const int tap = 16 * s + 4 * grp + (j >> 1), kc = j & 1;
-      if (s < 2 && tap < 27 && mrow < m_n) val = W[(mrow * CIN[l] + kc) * 27 + tap];
+    if (ci_n < 16) {
+      // one or two K channels: k = 8 grp + j -> tap (32 s + k) / ci_n, channel j % ci_n (ci_n steps)
+      const int tap = (32 * s + 8 * grp + j) / ci_n, kc = j % ci_n;
+      if (s < ci_n && tap < 27 && mrow < m_n)
+        val = flip ? W[(kc * CIN[l] + mrow) * 27 + (26 - tap)] : W[(mrow * CIN[l] + kc) * 27 + tap];
     } else {
       const int half = grp >> 1;
       const int tap = tap16(s, half);
