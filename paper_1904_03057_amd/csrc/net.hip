@@ -6,10 +6,10 @@
 // Activations are channels-last [voxel][16] bf16 (32 B per voxel); the first layer's input has
 // 2 channels, the last layer's output 1.  Every convolution is an implicit GEMM on
 // v_mfma_f32_16x16x32_bf16 computing Out^T = W^T In^T: M = 16 output channels (zero padded),
-// N = 16 voxels along x, K = 2 taps x 16 input channels per instruction (27 taps padded to 28).
+// N = 16 voxels along x, K = 2 taps x 16 input channels per instruction (27 taps padded to 30).
 // A workgroup stages its input tile (halo 1) in LDS with 16 channels per voxel and each wave
 // accumulates 16-voxel rows.  The same kernel runs the backward data pass with flipped,
-// transposed weights.  Weight gradients are a deterministic two-stage reduction (per-workgroup
+// transposed weights; the last layer has a kernel of its own (conv_last).  Weight gradients are a deterministic two-stage reduction (per-workgroup
 // partial sums on the matrix cores, then a fixed-order sum).  Optimiser: Adam on FP32 master weights.
 #include <hip/hip_runtime.h>
 
@@ -87,7 +87,7 @@ struct Grid3 {
 // ------------------------------------------------------------------------------------------
 // convolution on the matrix cores
 
-enum Epi { EPI_GELU = 0, EPI_LINEAR = 1, EPI_BWD = 2, EPI_RAW = 3, EPI_GELU_Z = 4 };
+enum Epi { EPI_GELU = 0, EPI_BWD = 2, EPI_RAW = 3, EPI_GELU_Z = 4 };
 
 // Geometry of the z-marching convolution: a workgroup owns a 32 x 8 column of output voxels and
 // marches through a chunk of zc planes, keeping the three input planes a output plane needs in an
@@ -100,12 +100,12 @@ constexpr int WROWS = 2 * CTY / 4;                 // 16-voxel rows per wave per
 struct ConvGeo {
   int tx, ty, nch, zc;
 };
-// z-chunk length: about 2048 workgroups in flight on small grids, at most 96 planes per chunk
-__host__ __device__ inline ConvGeo conv_geo(const Grid3& g) {
+// z-chunk length: about `wgs` workgroups on small grids, at most 96 planes per chunk
+__host__ __device__ inline ConvGeo conv_geo(const Grid3& g, int wgs = 2048) {
   ConvGeo c;
   c.tx = (g.nx + CTX - 1) / CTX;
   c.ty = (g.ny + CTY - 1) / CTY;
-  int64_t zc = (int64_t)g.nz * c.tx * c.ty / 2048;
+  int64_t zc = (int64_t)g.nz * c.tx * c.ty / wgs;
   c.zc = (int)(zc < 4 ? 4 : (zc > 96 ? 96 : zc));
   c.nch = (g.nz + c.zc - 1) / c.zc;
   return c;
@@ -133,7 +133,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // in: [voxel][CIS] bf16; wpk: packed A operands [steps][64 lanes][8]; out per epilogue:
 //   EPI_GELU:   yout (bf16 [voxel][16]) = GELU(z), z = acc + bias
 //   EPI_GELU_Z: as EPI_GELU, and zout (f32 [voxel][16]) = z
-//   EPI_LINEAR: fout (f32 [voxel]) = (acc[0] + bias[0]) * (*scale)          (last layer, 1 channel)
 //   EPI_BWD:    yout (bf16 [voxel][16]) = acc * GELU'(zprev[voxel][c])       (backward data)
 //   EPI_RAW:    fout (f32 [voxel][COS]) = acc (+ bias if bias != NULL)       (parity probes)
 // Two K layouts: with 16 input channels each K-step holds 2 taps x 16 channels (15 steps, order
@@ -149,8 +148,7 @@ template <int CIS, int COS, int EPI>
 __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
                                                  const float* __restrict__ bias, Grid3 g,
                                                  float* __restrict__ zout, uint16_t* __restrict__ yout,
-                                                 float* __restrict__ fout, const float* __restrict__ zprev,
-                                                 const double* __restrict__ scale) {
+                                                 float* __restrict__ fout, const float* __restrict__ zprev) {
   constexpr bool TAPS = (CIS < 16);                 // K runs over taps x CIS channels
   constexpr int STEPS = TAPS ? CIS : NSTEP;
   constexpr int VW = CIS;                           // bf16 per staged voxel
@@ -325,8 +323,6 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
             packed.x = pack_bf16x2(gelu_f(z[0]), gelu_f(z[1]));
             packed.y = pack_bf16x2(gelu_f(z[2]), gelu_f(z[3]));
             *(uint2*)(yout + vi * 16 + c0) = packed;
-          } else if (EPI == EPI_LINEAR) {
-            if (grp == 0) fout[vi] = (float)(((double)A[0] + (double)bz[0]) * scale[0]);
           } else if (EPI == EPI_BWD) {
             uint2 packed;
             packed.x = pack_bf16x2(A[0] * gelu_grad_f(zp[r].x), A[1] * gelu_grad_f(zp[r].y));
@@ -354,6 +350,115 @@ __global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in
           if (i + 4 <= zc + 1) fetch(i + 4);
         }
       }
+    }
+  }
+}
+
+// The last layer, 16 channels -> 1: fout (f32 [voxel]) = (acc + bias[0]) * (*scale), or acc + bias[0] without
+// a scale.  With one output channel the 16 rows of the A operand hold taps instead: row 4 dz + dy (dz, dy
+// = 0..2; the others zero) contracts the 3 taps along x (two K-steps: dx 0 and 1, then dx 2 and a
+// zero-weight partner), so an input row gives nine partial sums, which the vector ALU adds to the output
+// rows they belong to: 12 matrix instructions per 64 voxels of an input plane, where a row per output
+// channel takes 60 and keeps three planes in LDS.  Lane group dz of the D layout holds the sums of output
+// plane z + 1 - dz (z: the input plane), four rows in its registers; after a plane, group 2's are complete
+// and the others move on by one group.
+//
+// 256^3: 146 us (4.1 TB/s; 126 us at the copy rate) against 237 with a row per output channel, 128^3: 23
+// against 36 us.
+//
+// z-chunks for 1024 workgroups, four per CU of the six that registers allow: longer chunks read fewer halo
+// planes, 149 us at 256^3 against 156 (2048 workgroups) and 159 us (4096).
+constexpr int kLastWgs = 1024;
+
+__global__ __launch_bounds__(256, 6) void conv_last(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
+                                                 const float* __restrict__ bias, Grid3 g, float* __restrict__ fout,
+                                                 const double* __restrict__ scale) {
+  constexpr int UNITS = 2 * PLV, UPT = (UNITS + 255) / 256;  // 16-byte load units per plane, per thread
+  __shared__ __attribute__((aligned(16))) uint16_t st[2 * PLV * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const ConvGeo geo = conv_geo(g, kLastWgs);
+  const int64_t plane = (int64_t)g.nx * g.ny;
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  const int bx = bid % geo.tx, by = (bid / geo.tx) % geo.ty, ch = bid / (geo.tx * geo.ty);
+  const int x0 = bx * CTX, y0 = by * CTY, z0 = ch * geo.zc;
+  const int zc = min(geo.zc, g.nz - z0);
+
+  bf16x8 wa[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) wa[s] = *(const bf16x8*)(wpk + (s * 64 + lane) * 8);
+  const float b0 = bias[0];
+  const int grp = lane >> 4, vx = lane & 15;
+
+  // this thread's load units: plane-relative global voxel offsets (-1: outside a Dirichlet grid)
+  int uoff[UPT];
+#pragma unroll
+  for (int q = 0; q < UPT; ++q) {
+    const int u = tid + 256 * q, v = u >> 1;
+    int gx = x0 - 1 + v % SX, gy = y0 - 1 + v / SX;
+    bool ok = u < UNITS;
+    if (g.periodic) {
+      gx = (gx + g.nx) % g.nx;
+      gy = (gy + g.ny) % g.ny;
+    } else {
+      ok = ok && gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny;
+    }
+    uoff[q] = ok ? gy * g.nx + gx : -1;
+  }
+  uint4 pre[UPT];
+  auto fetch = [&](int j) {  // relative plane j (global plane z0 - 1 + j)
+    int gz = z0 - 1 + j;
+    bool pv = true;
+    if (g.periodic) gz = (gz + g.nz) % g.nz;
+    else pv = gz >= 0 && gz < g.nz;
+    const int64_t pb = (int64_t)gz * plane;
+#pragma unroll
+    for (int q = 0; q < UPT; ++q) {
+      pre[q] = make_uint4(0, 0, 0, 0);
+      if (pv && uoff[q] >= 0) pre[q] = ((const uint4*)(in + (pb + uoff[q]) * 16))[tid & 1];
+    }
+  };
+  auto stash = [&](int slot) {
+#pragma unroll
+    for (int q = 0; q < UPT; ++q) {
+      const int u = tid + 256 * q;
+      if (u < UNITS) ((uint4*)st)[slot * UNITS + u] = pre[q];
+    }
+  };
+  // wave w owns rows y = 4 (w >> 1) + r (r = 0..3) of x half w & 1; k = 8 grp + j: dx grp >> 1 (step 0) or 2
+  // (step 1; its partner reads the same voxel), channel 8 (grp & 1) + j
+  const int yb = 4 * (wave >> 1), xh = wave & 1;
+  const int l1 = (yb * SX + xh * 16 + vx) * 16 + (grp & 1) * 8, l0 = l1 + (grp >> 1) * 16;
+
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};  // rows yb + r of output plane z + 1 - grp
+  fetch(0);
+  stash(0);
+  fetch(1);
+  for (int j = 0; j < zc + 2; ++j) {
+    __syncthreads();  // plane j is in its slot, and the other slot has been read
+    if (j < zc + 1) stash((j + 1) & 1);
+    if (j < zc) fetch(j + 2);
+    const uint16_t* sp = st + (j & 1) * PLV * 16;
+    f32x4 p[WROWS + 2];
+#pragma unroll
+    for (int yy = 0; yy < WROWS + 2; ++yy) {
+      p[yy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[0], *(const bf16x8*)(sp + l0 + yy * SX * 16),
+                                                      f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      p[yy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[1], *(const bf16x8*)(sp + l1 + (yy * SX + 2) * 16), p[yy], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < WROWS; ++r) acc[r] += (p[r][0] + p[r + 1][1]) + p[r + 2][2];
+    if (j >= 2 && grp == 2) {
+      const int gx = x0 + xh * 16 + vx;
+      float* o = fout + (int64_t)(z0 + j - 2) * plane + (int64_t)(y0 + yb) * g.nx + gx;
+#pragma unroll
+      for (int r = 0; r < WROWS; ++r)
+        if (gx < g.nx && y0 + yb + r < g.ny)
+          o[(int64_t)r * g.nx] = scale ? (float)(((double)acc[r] + (double)b0) * scale[0]) : acc[r] + b0;
+    }
+#pragma unroll
+    for (int r = 0; r < WROWS; ++r) {
+      const float v = __shfl_up(acc[r], 16);
+      acc[r] = grp == 0 ? 0.f : v;
     }
   }
 }
@@ -759,7 +864,7 @@ __global__ __launch_bounds__(256) void adam(float* __restrict__ w, float* __rest
 // Packed A operands of every layer, one wave per (K-step blockIdx.x, layer blockIdx.y, direction
 // blockIdx.z): one launch for the eight that took 25 us each with a wave per layer.  Forward (z = 0):
 // A[m][k] = W[m][ci][tap] with tap = tap16(s, k >> 4), ci = k & 15 (zero outside the layer's channels
-// and for the padding partners of steps 12-14).  Backward data (z = 1): the transposed convolution's
+// and for the padding partners of steps 12-14; one row per tap for the last layer).  Backward data (z = 1): the transposed convolution's
 // weights W'[ci][co][tap] = W[co][ci][26 - tap], M = ci, K = (tap, co).
 // Lane layout of v_mfma_f32_16x16x32_bf16 A: lane holds row (lane & 15), k = 8 (lane >> 4) + j.
 __global__ __launch_bounds__(64) void pack_weights(const float* __restrict__ w, uint16_t* __restrict__ wf,
@@ -773,7 +878,12 @@ __global__ __launch_bounds__(64) void pack_weights(const float* __restrict__ w, 
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     float val = 0.f;
-    if (ci_n < 16) {
+    if (!flip && m_n == 1) {
+      // last layer: row 4 dz + dy, k = 8 grp + j -> dx grp / 2 (s = 0) or 2 (s = 1), channel 8 (grp % 2) + j
+      const int dz = mrow >> 2, dy = mrow & 3, dx = s == 0 ? grp >> 1 : 2;
+      if (dz < 3 && dy < 3 && (s == 0 || (s == 1 && grp < 2)))
+        val = W[((grp & 1) * 8 + j) * 27 + 9 * dz + 3 * dy + dx];
+    } else if (ci_n < 16) {
       // one or two K channels: k = 8 grp + j -> tap (32 s + k) / ci_n, channel j % ci_n (ci_n steps)
       const int tap = (32 * s + 8 * grp + j) / ci_n, kc = j % ci_n;
       if (s < ci_n && tap < 27 && mrow < m_n)
@@ -981,9 +1091,9 @@ static int check_grid(const tbs_net* n, const int64_t grid[3]) {
 }
 
 // one workgroup per (32 x 8 column, z-chunk)
-static int conv_blocks(const int64_t grid[3]) {
+static int conv_blocks(const int64_t grid[3], int wgs = 2048) {
   const Grid3 g{(int)grid[0], (int)grid[1], (int)grid[2], 0};
-  const ConvGeo c = conv_geo(g);
+  const ConvGeo c = conv_geo(g, wgs);
   return c.tx * c.ty * c.nch;
 }
 
@@ -1000,17 +1110,16 @@ static int forward_layers(tbs_net* n, Grid3 g, int keep, float* out) {
 #define GELU_LAYER(CI, IN, L, Y)                                                                                       \
   if (keep)                                                                                                            \
     hipLaunchKernelGGL((conv_mfma<CI, 16, EPI_GELU_Z>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)(IN),          \
-                       w.wf + (L) * PACK, w.bias + 16 * (L), g, w.z[L], Y, nullptr, nullptr, nullptr);                 \
+                       w.wf + (L) * PACK, w.bias + 16 * (L), g, w.z[L], Y, nullptr, nullptr);                          \
   else                                                                                                                 \
     hipLaunchKernelGGL((conv_mfma<CI, 16, EPI_GELU>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)(IN),            \
-                       w.wf + (L) * PACK, w.bias + 16 * (L), g, nullptr, Y, nullptr, nullptr, nullptr)
+                       w.wf + (L) * PACK, w.bias + 16 * (L), g, nullptr, Y, nullptr, nullptr)
   GELU_LAYER(2, w.x0, 0, w.y[0]);
   GELU_LAYER(16, w.y[0], 1, w.y[1]);
   GELU_LAYER(16, w.y[1], 2, y2);
 #undef GELU_LAYER
-  hipLaunchKernelGGL((conv_mfma<16, 1, EPI_LINEAR>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)y2,
-                     w.wf + 3 * PACK, w.bias + 48, g, nullptr, nullptr, w.o, nullptr,
-                     (const double*)(w.sc + (keep ? 3 : 2)));
+  hipLaunchKernelGGL(conv_last, dim3(conv_blocks(grid, kLastWgs)), dim3(256), 0, n->st, (const uint16_t*)y2,
+                     w.wf + 3 * PACK, w.bias + 48, g, w.o, (const double*)(w.sc + (keep ? 3 : 2)));
   NCHK(hipGetLastError());
   // output low-pass (linear, so it commutes with the output scale); scratch: a free activation buffer
   return smooth(n, w.o, keep ? (float*)w.gz[0] : (float*)w.y[1], out, g);
@@ -1105,21 +1214,21 @@ extern "C" int tbs_net_train_step(tbs_net* n, const float* u, const float* q, co
     hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 27 + 1 + 63) / 64), dim3(1024), 0, n->st, (const float*)w.part,
                        wblocks, 16 * 27 + 1, w.grad + woff(3), acc);
     hipLaunchKernelGGL((conv_mfma<1, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gout,
-                       w.wb + 3 * PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[2], nullptr);
+                       w.wb + 3 * PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[2]);
     // layer 3: dW3 = sum y2 (x) dZ3 ; dZ2 = convT(dZ3, W3) * GELU'(z2)
     hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks16), dim3(256), 0, n->st, (const uint16_t*)w.y[1],
                        (const uint16_t*)w.gz[0], g, w.part);
     hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 63) / 64), dim3(1024), 0, n->st,
                        (const float*)w.part, kPartBlocks16, 16 * 16 * 27 + 16, w.grad + woff(2), acc);
     hipLaunchKernelGGL((conv_mfma<16, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gz[0],
-                       w.wb + 2 * PACK, nullptr, g, nullptr, w.gz[1], nullptr, (const float*)w.z[1], nullptr);
+                       w.wb + 2 * PACK, nullptr, g, nullptr, w.gz[1], nullptr, (const float*)w.z[1]);
     // layer 2: dW2 = sum y1 (x) dZ2 ; dZ1 = convT(dZ2, W2) * GELU'(z1)
     hipLaunchKernelGGL((wgrad_partial<16, 16>), dim3(kPartBlocks16), dim3(256), 0, n->st, (const uint16_t*)w.y[0],
                        (const uint16_t*)w.gz[1], g, w.part);
     hipLaunchKernelGGL(wgrad_reduce, dim3((16 * 16 * 27 + 16 + 63) / 64), dim3(1024), 0, n->st,
                        (const float*)w.part, kPartBlocks16, 16 * 16 * 27 + 16, w.grad + woff(1), acc);
     hipLaunchKernelGGL((conv_mfma<16, 16, EPI_BWD>), dim3(nb), dim3(256), 0, n->st, (const uint16_t*)w.gz[1],
-                       w.wb + PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[0], nullptr);
+                       w.wb + PACK, nullptr, g, nullptr, w.gz[0], nullptr, (const float*)w.z[0]);
     // layer 1: dW1 = sum x0 (x) dZ1
     hipLaunchKernelGGL((wgrad_partial<2, 16>), dim3(wblocks), dim3(256), 0, n->st, (const uint16_t*)w.x0,
                        (const uint16_t*)w.gz[0], g, w.part);
@@ -1156,15 +1265,17 @@ extern "C" int tbs_net_conv_layer(tbs_net* n, int layer, int mode, const uint16_
   if (mode == 0) {  // forward pre-activation z = conv(x, W) + b, out [voxel][co]
     if (!aligned256(x)) return TBS_E_INVAL;
 #define FWD(CI, CO) hipLaunchKernelGGL((conv_mfma<CI, CO, EPI_RAW>), dim3(nb), dim3(256), 0, n->st, x, \
-                                       w.wf + layer * PACK, w.bias + layer * 16, g, nullptr, nullptr, out, nullptr, nullptr)
+                                       w.wf + layer * PACK, w.bias + layer * 16, g, nullptr, nullptr, out, nullptr)
     if (ci == 2) FWD(2, 16);
     else if (co == 16) FWD(16, 16);
-    else FWD(16, 1);
+    else
+      hipLaunchKernelGGL(conv_last, dim3(conv_blocks(n->grid, kLastWgs)), dim3(256), 0, n->st, x,
+                         w.wf + layer * PACK, w.bias + layer * 16, g, out, (const double*)nullptr);
 #undef FWD
   } else if (mode == 1) {  // data gradient dx = convT(g, W), out [voxel][ci]
     if (!aligned256(gin)) return TBS_E_INVAL;
 #define BWD(CI, CO) hipLaunchKernelGGL((conv_mfma<CI, CO, EPI_RAW>), dim3(nb), dim3(256), 0, n->st, gin, \
-                                       w.wb + layer * PACK, nullptr, g, nullptr, nullptr, out, nullptr, nullptr)
+                                       w.wb + layer * PACK, nullptr, g, nullptr, nullptr, out, nullptr)
     if (co == 1) BWD(1, 16);
     else if (ci == 2) BWD(16, 2);
     else BWD(16, 16);

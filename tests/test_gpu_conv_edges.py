@@ -32,3 +32,33 @@ def test_data_grad_tile_edges(circular, grid, layer):
     # exact products, 27 co of them and their roundings in FP32
     tol = 27 * co * 2.0 ** -23 * cnn.conv3d_data_grad(np.abs(g), np.abs(W), circular)
     assert np.all(np.abs(_from_cl(out) - ref) <= tol)
+
+
+@pytest.mark.parametrize("circular", [False, True])
+@pytest.mark.parametrize("grid", GRIDS + [(161, 130, 70)])   # the last: chunks of several planes, ragged
+def test_last_layer_tile_edges(circular, grid):
+    print("last layer", circular, grid, flush=True)
+    theta = cnn_init(7)
+    theta[cnn.N_PARAMS - 1] = 0.25
+    net = _net(grid, theta=theta)
+    W = cnn.unpack(to_bf16(theta))[3][0]
+    x = to_bf16(normal_field((16,) + grid[::-1], 70))
+    out = torch.full(grid[::-1] + (1,), float("nan"), dtype=torch.float32, device="cuda")
+    net.conv_layer(3, 0, _cl(x), None, circular, out)
+    ref = cnn.conv3d(x, W, np.array([0.25]), circular)
+    # exact products, 432 of them, the bias and their roundings in FP32
+    tol = 433 * 2.0 ** -23 * (cnn.conv3d(np.abs(x), np.abs(W), None, circular) + 0.25)
+    assert np.all(np.abs(_from_cl(out) - ref) <= tol)
+
+
+def test_last_layer_keeps_an_infinity_to_its_stencil():
+    grid = (40, 12, 9)
+    net = _net(grid, theta=cnn_init(7))
+    x = to_bf16(normal_field((16,) + grid[::-1], 71))
+    x[3, 4, 5, 17] = np.inf
+    out = torch.empty(grid[::-1] + (1,), dtype=torch.float32, device="cuda")
+    net.conv_layer(3, 0, _cl(x), None, False, out)
+    bad = ~np.isfinite(host(out)[..., 0])
+    near = np.zeros_like(bad)
+    near[3:6, 4:7, 16:19] = True
+    assert np.array_equal(bad, near)
