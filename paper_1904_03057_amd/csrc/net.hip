@@ -142,10 +142,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // reads of the B operands use immediate offsets.
 //
 // The backward data pass moves 96 (1 -> 16 channels) or 128 bytes per voxel, 42 or 56 us at 128^3 at the
-// copy rate, and takes 53 or 68 us there; 88 or 83 us with 1 channel padded to 16, GELU' from erff and expf
+// copy rate, and takes 50 or 64 us there; 88 or 83 us with 1 channel padded to 16, GELU' from erff and expf
 // and z loaded only after the products.
+//
+// The launch bound is the occupancy these kernels have anyhow (three or four waves per SIMD); said aloud it
+// makes the compiler keep the accumulators out of the accumulation registers, whose contents the epilogue
+// would first have to move: 64 against 69 us (16 -> 16 backward), 68 against 71 us (forward, storing z).
 template <int CIS, int COS, int EPI>
-__global__ __launch_bounds__(256) void conv_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
+__global__ __launch_bounds__(256, CIS == 16 ? 3 : 4) void conv_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wpk,
                                                  const float* __restrict__ bias, Grid3 g,
                                                  float* __restrict__ zout, uint16_t* __restrict__ yout,
                                                  float* __restrict__ fout, const float* __restrict__ zprev) {
