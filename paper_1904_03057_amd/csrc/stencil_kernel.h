@@ -31,8 +31,12 @@ template <typename T> __device__ __forceinline__ T fmad(T a, T b, T c);
 template <> __device__ __forceinline__ float fmad<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 template <> __device__ __forceinline__ double fmad<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// VE consecutive elements (one 16-byte access for the staged input, or a single element).
-template <typename T, int VE> struct alignas(sizeof(T) * VE) VecN { T x[VE]; };
+// VE consecutive elements (one 16-byte access for the staged input, or a single element).  A vector
+// type, not an array: accesses to an array in LDS come out as pairs of single elements, which lanes two or four
+// elements apart read and write with bank conflicts (3.3 conflict cycles per LDS instruction of the FP32 apply;
+// 928^3 cubic 1.62 against 1.69 ms, quintic FP64 step 49.7 against 51.2 ms, FP64 iteration at 32^3 18.8 against
+// 19.5 us).
+template <typename T, int VE> struct VecN { T x __attribute__((ext_vector_type(VE))); };
 
 template <typename Ts, typename Tc> __device__ __forceinline__ Tc to_c(Ts v) { return (Tc)v; }
 template <> __device__ __forceinline__ float to_c<uint16_t, float>(uint16_t v) { return bf16_to_f32(v); }
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
   constexpr int QD = CG ? N + 1 : 1;  // depth of the centre-value rings (CG1, CGF)
   static_assert(TY % WY == 0, "TY must be a multiple of the row waves");
 
-  __shared__ __attribute__((aligned(16))) Tc stage[R * C];
+  __shared__ __attribute__((aligned(32))) Tc stage[R * C];
   __shared__ __attribute__((aligned(16))) Tc su[R * TX];
   __shared__ __attribute__((aligned(16))) Tc sv[R * TX];
   __shared__ Tc cring[QD * TY * TX];  // p at the own points of the last n+1 planes (p.q)
@@ -76,7 +80,7 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
   // before the barrier that follows, so it keeps one plane more than cring: the slot being written
   // is never the one the previous plane's outputs are still reading.
   constexpr int RQD = FUSED ? N + 2 : 1;
-  __shared__ Tc rring[FUSED ? RQD * TY * TX : 1];
+  __shared__ __attribute__((aligned(32))) Tc rring[FUSED ? RQD * TY * TX : 1];
   __shared__ double red[4][WY * WX];
   __shared__ bool last;  // CGF: this workgroup is the last to finish
   // BC_ROBIN: corner blocks in compute precision (cm, cvx, cwy, cwz, each kRobinMaxZ^2)
@@ -266,13 +270,13 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       if (soff[v] >= 0) {
-        Tc* dst = stage + soff[v];
+        RawC dst;
         if (MODE == M_APPLY || RES) {
 #pragma unroll
-          for (int e = 0; e < VE; ++e) dst[e] = to_c<Tin, Tc>(pa[sl][v].x[e]);
+          for (int e = 0; e < VE; ++e) dst.x[e] = to_c<Tin, Tc>(pa[sl][v].x[e]);
         } else if (MODE == M_RHS) {
 #pragma unroll
-          for (int e = 0; e < VE; ++e) dst[e] = fmad(tauc, pb[sl][v].x[e], to_c<Tin, Tc>(pa[sl][v].x[e]));
+          for (int e = 0; e < VE; ++e) dst.x[e] = fmad(tauc, pb[sl][v].x[e], to_c<Tin, Tc>(pa[sl][v].x[e]));
         } else {
           Raw pn;
           RawC xn, rn;
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
             // CGF: r_k = r_{k-1} - alpha_{k-1} q_{k-1} at every staged point (halo included)
             if (FUSED && !a.first) rv = fmad(-alpha_prev, pq[FUSED ? sl : 0][FUSED ? v : 0].x[e], rv);
             const Tc val = storage_round<Tin, Tc>(fmad(beta, pold, rv));
-            dst[e] = val;
+            dst.x[e] = val;
             pn.x[e] = from_c<Tin, Tc>(val);
             rn.x[e] = rv;
             if (v < NVC) {
@@ -295,8 +299,8 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
           }
           if (FUSED && v < NVC) {
             const int rs = ((k % RQD) + RQD) % RQD;
-#pragma unroll
-            for (int e = 0; e < VE; ++e) rring[rs * TY * TX + coff[v < NVC ? v : 0] + e] = rn.x[e];
+            Tc* at = rring + rs * TY * TX + coff[v < NVC ? v : 0];
+            *(RawC*)at = rn;
           }
           if (ow) {
             const int64_t gi = base + off[v];
@@ -309,6 +313,8 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
             }
           }
         }
+        Tc* at = stage + soff[v];  // a variable: cast in place, the sum keeps the alignment of one element
+        *(RawC*)at = dst;
       }
     }
   };
