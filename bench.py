@@ -197,7 +197,7 @@ def main():
 
 # the sources of the stencil kernels and of their launch geometry (the host's tile / z-chunk plan):
 # a traffic summary holds only while they hash as measured
-STENCIL_SOURCES = ("stencil_kernel.h", "stencil.hip", "stencil.h", "common.h")
+STENCIL_SOURCES = ("stencil_kernel.h", "stencil.hip", "stencil.h", "common.h", "cg_finish.h")
 
 
 def stencil_sources_hash():
@@ -692,8 +692,8 @@ def workload_steps(tbs, torch):
 
 
 def transforms(tbs, torch, w, u0):
-    """Indirect transform (evaluation at the nodes, FP64) and direct transform (FP64 CG on the
-    evaluation operator to 1e-12, started from the samples) of the workload's field, cubic."""
+    """Indirect transform (evaluation at the nodes, FP64) and direct transform (separable banded solves on the FP64
+    residual to 1e-12, started from the samples) of the workload's field, cubic."""
     N = w.grid[0] * w.grid[1] * w.grid[2]
     t = tbs.Transform(w.grid, w.degree, w.bc)
     t.ensure_workspace(tbs.PREC_FP64)

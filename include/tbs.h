@@ -109,8 +109,7 @@ typedef struct {
                               prediction r.r - 2 alpha r.q + alpha^2 q.q; 0 = the two-kernel
                               Hestenes-Stiefel iteration (q = A p and p.q, then r -= alpha q and r.r).
                               FP32 (TBS_PREC_FP32, MIXED, MIXED_BF16, tbs_cg_step in F32) and FP64
-                              (TBS_PREC_FP64, tbs_cg_step in F64, tbs_transform_interp and the
-                              coarse-grid solve) alike. */
+                              (TBS_PREC_FP64, tbs_cg_step in F64 and the coarse-grid solve) alike. */
   int coarse_guess;        /* 1: tbs_timestep without a network starts from a coarse-grid guess
                               (Sec. 3 leg example: CG started from a reduced-grid solution): the
                               residual of u_prev is restricted to the halved grid, the coarse
