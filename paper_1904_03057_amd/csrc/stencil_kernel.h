@@ -72,7 +72,10 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
   constexpr int QD = CG ? N + 1 : 1;  // depth of the centre-value rings (CG1, CGF)
   static_assert(TY % WY == 0, "TY must be a multiple of the row waves");
 
-  __shared__ __attribute__((aligned(32))) Tc stage[R * C];
+  // whole vectors are written to stage and rring: a vector type's alignment is its size (64 bytes for bf16 -> FP64)
+  constexpr int SA = alignof(RawC) > 32 ? alignof(RawC) : 32;
+  static_assert(SA >= alignof(RawC) && C % VE == 0 && TX % VE == 0, "every staged vector is aligned");
+  __shared__ __attribute__((aligned(SA))) Tc stage[R * C];
   __shared__ __attribute__((aligned(16))) Tc su[R * TX];
   __shared__ __attribute__((aligned(16))) Tc sv[R * TX];
   __shared__ Tc cring[QD * TY * TX];  // p at the own points of the last n+1 planes (p.q)
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(64 * WX * WY) __attribute__((amdgpu_waves_per_eu(st
   // before the barrier that follows, so it keeps one plane more than cring: the slot being written
   // is never the one the previous plane's outputs are still reading.
   constexpr int RQD = FUSED ? N + 2 : 1;
-  __shared__ __attribute__((aligned(32))) Tc rring[FUSED ? RQD * TY * TX : 1];
+  __shared__ __attribute__((aligned(SA))) Tc rring[FUSED ? RQD * TY * TX : 1];
   __shared__ double red[4][WY * WX];
   __shared__ bool last;  // CGF: this workgroup is the last to finish
   // BC_ROBIN: corner blocks in compute precision (cm, cvx, cwy, cwz, each kRobinMaxZ^2)
