@@ -1212,10 +1212,11 @@ extern "C" int tbs_timestep(tbs_ctx* c, const double* u_prev, const double* q, d
       a.in0 = du;
       a.out0 = adu;
       HIPCHK(launch_apply(a, c->n, c->bc, 1, 1, c->st));
-      HIPCHK(launch_dot(r0, du, c->N, 1, part0(c), c->st));
-      HIPCHK(launch_finalize(FIN_DOT, part0(c), nullptr, kVecBlocks, scal(c, 2), 0.0, c->st));
-      HIPCHK(launch_dot(du, adu, c->N, 1, part0(c), c->st));
-      HIPCHK(launch_finalize(FIN_DOT, part0(c), nullptr, kVecBlocks, scal(c, 3), 0.0, c->st));
+      // (in part2: part0 keeps the sums of r0, from which the first sweep starts if the guess is rejected)
+      HIPCHK(launch_dot(r0, du, c->N, 1, part2(c), c->st));
+      HIPCHK(launch_finalize(FIN_DOT, part2(c), nullptr, kVecBlocks, scal(c, 2), 0.0, c->st));
+      HIPCHK(launch_dot(du, adu, c->N, 1, part2(c), c->st));
+      HIPCHK(launch_finalize(FIN_DOT, part2(c), nullptr, kVecBlocks, scal(c, 3), 0.0, c->st));
       Scalars d1, d2;
       rc = read_scal(c, SC_AUX, &res0);
       if (!rc) rc = read_scal(c, 2, &d1);
