@@ -362,7 +362,8 @@ int tbs_net_get_grad(const tbs_net* net, float* host, size_t n);
  * 6 cg-fused f32, 7 cg-fused f32 with bf16 p, 8 residual f64, 9 cg-update f64, 10 cg-update f32,
  * 11 one-kernel CG iteration f32, 12 one-kernel CG iteration f32 with bf16 p, 13 variable-coefficient
  * apply f64, 14 variable-coefficient apply f32 (bytes: u, d, m read and y written once), 15 one-kernel
- * CG iteration f64, 16 fused rhs and residual f64 (u read, b and the FP32 r written). */
+ * CG iteration f64 (with the launch that adds its sums, where a Robin box has one: the time of both, the
+ * bytes and the count of the iteration), 16 fused rhs and residual f64 (u read, b and the FP32 r written). */
 #define TBS_PROF_KINDS 17
 int tbs_prof_enable(tbs_ctx* ctx, int on);   /* resets the counters */
 int tbs_prof_read(tbs_ctx* ctx, int kind, double* total_ms, double* total_bytes, int64_t* launches);

@@ -865,7 +865,6 @@ static int cgf_async(tbs_ctx* c, const CgArrays& A, int dt, int k, bool publish)
     a.status = nullptr;
   }
   HIPCHK(launch_cgf(a, c->n, c->bc, dt, c->st));
-  prof_end(c, ps);
   if (apart) {
     d.in0 = a.out2;
     d.in1 = a.out1;
@@ -874,6 +873,7 @@ static int cgf_async(tbs_ctx* c, const CgArrays& A, int dt, int k, bool publish)
     d.nchunks = (int)((c->nz + d.zc - 1) / d.zc);
     HIPCHK(launch_cg_dots(d, c->n, c->st));
   }
+  prof_end(c, ps);  // one record for both launches
   return TBS_OK;
 }
 
