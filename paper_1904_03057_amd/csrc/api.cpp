@@ -1074,14 +1074,27 @@ extern "C" int tbs_transform_interp(tbs_ctx* c, const double* samples, double* c
     Scalars s;
     rc = read_scal(c, SC_AUX, &s);
     if (rc) return rc;
-    rel = s.out2 > 0 ? std::sqrt(s.out / s.out2) : std::sqrt(s.out);
     if (!std::isfinite(s.out) || !std::isfinite(s.out2)) {
+      rel = s.out2 > 0 ? std::sqrt(s.out / s.out2) : std::sqrt(s.out);
       result = set_err(TBS_E_BREAKDOWN, "non-finite residual after %d iterations", nit);
+      break;
+    }
+    const double rr = s.out;
+    if (s.out2 < 0x1p-900) {  // zero samples, or samples whose squares underflow: norms at a scale where none does
+      rc = resid_async(c, coef, samples, nullptr, TBS_F64, SC_AUX, FIN_NORMS, 0.0, 0x1p600);
+      if (!rc) rc = read_scal(c, SC_AUX, &s);
+      if (rc) return rc;
+    }
+    rel = std::sqrt(s.out2 > 0 ? s.out / s.out2 : rr);
+    if (s.out2 == 0.0 && s.out > 0.0 && nit < max_iter) {  // zero samples: the coefficients are zero
+      HIPCHK(launch_fill(coef, 0, c->N, c->st));
+      rel = 0.0;
+      result = TBS_OK;
       break;
     }
     // near FP64 precision the residual is its own rounding, and rtol may be below that: no further gain
     const bool at_rounding = rtol > 0.0 && nit > 1 && rel <= 1e-14 && rel >= 0.5 * before;
-    if (s.out2 == 0.0 || s.out <= rtol * rtol * s.out2 || at_rounding) { result = TBS_OK; break; }
+    if (s.out <= rtol * rtol * s.out2 || at_rounding) { result = TBS_OK; break; }
     if (nit >= max_iter) { result = TBS_W_NOT_CONVERGED; break; }
     before = rel;
     HIPCHK(launch_band_solve(r, coef, dims, c->n, c->bc == TBS_BC_PERIODIC, f, c->st));
