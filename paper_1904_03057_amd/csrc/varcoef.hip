@@ -329,10 +329,13 @@ static hipError_t launch_nt(const VarcoefArgs& a, int bc, hipStream_t st) {
   VarcoefTab<T> tab{};
   auto bv = [&](int q, int t) { return a.bv[q * kVcMaxB + t]; };
   auto bd = [&](int q, int t) { return a.bd[q * kVcMaxB + t]; };
+  // The kernel sums pairs of coefficients and of point products: the two interpolations before the x-axis
+  // carry a factor 1/2 each, so that neither overflows where the result does not, and the x-axis
+  // projection of the products of two fields a factor 16 (powers of two: no rounding changes).
   for (int q = 0; q < Q; ++q)
     for (int t = 0; t < NB; ++t) {
-      tab.v[q][t] = (T)bv(q, t);
-      tab.d[q][t] = (T)bd(q, t);
+      tab.v[q][t] = (T)(0.5 * bv(q, t));
+      tab.d[q][t] = (T)(0.5 * bd(q, t));
       tab.pv[q][t] = (T)(a.w[q] * bv(q, t));
       tab.pdy[q][t] = (T)(a.w[q] * bd(q, t) * a.ihy2);
       tab.pdz[q][t] = (T)(a.w[q] * bd(q, t) * a.ihz2);
@@ -345,16 +348,16 @@ static hipError_t launch_nt(const VarcoefArgs& a, int bc, hipStream_t st) {
       tab.xvo[q][t] = (T)vo;
       tab.xde[q][t] = (T)de;
       tab.xdo[q][t] = (T)dv;
-      tab.pve[q][t] = (T)(a.w[q] * ve);
-      tab.pvo[q][t] = (T)(a.w[q] * vo);
-      tab.pde[q][t] = (T)(a.w[q] * de * a.ihx2);
-      tab.pdo[q][t] = (T)(a.w[q] * dv * a.ihx2);
+      tab.pve[q][t] = (T)(16.0 * a.w[q] * ve);
+      tab.pvo[q][t] = (T)(16.0 * a.w[q] * vo);
+      tab.pde[q][t] = (T)(16.0 * a.w[q] * de * a.ihx2);
+      tab.pdo[q][t] = (T)(16.0 * a.w[q] * dv * a.ihx2);
     }
     if (NB % 2) {
       tab.xve[q][NP] = (T)bv(q, NP);
       tab.xde[q][NP] = (T)bd(q, NP);
-      tab.pve[q][NP] = (T)(a.w[q] * bv(q, NP));
-      tab.pde[q][NP] = (T)(a.w[q] * bd(q, NP) * a.ihx2);
+      tab.pve[q][NP] = (T)(16.0 * a.w[q] * bv(q, NP));
+      tab.pde[q][NP] = (T)(16.0 * a.w[q] * bd(q, NP) * a.ihx2);
     }
   }
   if (bc == BC_PERIODIC)
