@@ -482,9 +482,14 @@ __global__ __launch_bounds__(256, 6) void conv_last(const uint16_t* __restrict__
 //
 // The arrays read once take 28 us for 16 -> 16 channels at 128^3 and the matrix instructions 12 us;
 // the vector-ALU form this replaced took 2335 us there (16 -> 1: 298 us, 2 -> 16: 128 us), this one
-// 63 (38, 40) us.  What bounds it is the latency of a tile (fetch, two barriers, 112 matrix
+// 62 (41, 45) us.  What bounds it is the latency of a tile (fetch, two barriers, 112 matrix
 // instructions in one wave per SIMD): 85 us without the register prefetch of the next tile at two
 // workgroups per CU, 225 us with both (the prefetch spills).
+//
+// The narrow layers use 1 or 2 of an accumulator's 4 values and have more tiles to a workgroup's chain than the
+// vector-ALU form had voxels, so each tile is summed by itself and then added: error against 64 bits at
+// 128^3 9.1e-8 to 9.9e-8, 1.8e-7 to 2.0e-7 with one chain per workgroup (38 and 39 us), 1.0e-7 to 1.2e-7 in the
+// vector-ALU form.
 //
 // Each workgroup sums its tiles (grid stride) in registers and writes one row of partial sums (its
 // waves added in a fixed order); a second kernel adds the rows in a fixed order in FP64.
@@ -521,9 +526,18 @@ __global__ __launch_bounds__(256, CIS * COS == 256 ? 1 : 2) void wgrad_partial(c
     if (g.periodic) i = i == -1 ? n - 1 : (i == n ? 0 : i);
     return i >= 0 && i < n ? i : -1;
   };
+  // D layout: acc[t][r] = dW[co = 4 (lane >> 4) + r][ci = lane & 15]; with 2 input channels the operands change
+  // places, dW[co = lane & 15][ci = 4 (lane >> 4) + r].  A narrow layer's gradients are in the first KEEP values
+  // of a lane.  There each tile is summed by itself and then added, which keeps the FP32 chains short.
+  constexpr int KEEP = COS == 1 ? 1 : (CIS == 2 ? 2 : 4);
+  constexpr bool NARROW = KEEP < 4;
   f32x4 acc[WACC];
 #pragma unroll
   for (int t = 0; t < WACC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [](bf16x8 gv, bf16x8 xv, f32x4 c) {
+    return CIS == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, gv, c, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f32_16x16x32_bf16(gv, xv, c, 0, 0, 0);
+  };
   if (CIS < 16 || COS < 16)  // channels the layer does not have stay zero
     for (int i = tid; i < (WXV + WGV) * 2; i += 256) ((uint4*)st)[i] = make_uint4(0, 0, 0, 0);
 
@@ -590,35 +604,72 @@ __global__ __launch_bounds__(256, CIS * COS == 256 ? 1 : 2) void wgrad_partial(c
     if (tile + (int)gridDim.x < ntiles) fetch(tile + gridDim.x);
     __syncthreads();
     // X row (wave, y), tap (dz, dy, dx): G row (wave + 2 - dz, y + 2 - dy) of the stage
-    bf16x8 a[3][WTY + 2];
+    if constexpr (NARROW) {
+      // one G plane (dz) at a time, so that nine accumulators are in use beside the sums; the next plane's rows
+      // are read during the products
+      bf16x8 a[WTY + 2], nxt[WTY + 2];
+      auto rows = [&](int dz) {
 #pragma unroll
-    for (int dz = 0; dz < 3; ++dz)
+        for (int r = 0; r < WTY + 2; ++r) nxt[r] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + r) * WTX * 16, lane);
+      };
+      rows(0);
 #pragma unroll
-      for (int r = 0; r < 2; ++r) a[dz][r] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + r) * WTX * 16, lane);
+      for (int dz = 0; dz < 3; ++dz) {
+        __builtin_amdgcn_sched_barrier(0);  // not two planes ahead: the registers are full
 #pragma unroll
-    for (int y = 0; y < WTY; ++y) {
-      bf16x8 b[3];
+        for (int r = 0; r < WTY + 2; ++r) a[r] = nxt[r];
+        if (dz < 2) rows(dz + 1);
+        f32x4 part[10];
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) b[dx] = read_row_tr(xs + ((wave * WTY + y) * (WTX + 2) + dx) * 16, lane);
+        for (int t = 0; t < 10; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int dz = 0; dz < 3; ++dz)
-        a[dz][y + 2] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + y + 2) * WTX * 16, lane);
+        for (int y = 0; y < WTY; ++y) {
+          bf16x8 b[3];
 #pragma unroll
-      for (int dz = 0; dz < 3; ++dz)
+          for (int dx = 0; dx < 3; ++dx) b[dx] = read_row_tr(xs + ((wave * WTY + y) * (WTX + 2) + dx) * 16, lane);
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-          for (int dx = 0; dx < 3; ++dx) {
-            const int t = 9 * dz + 3 * dy + dx;
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[dz][y + 2 - dy], b[dx], acc[t], 0, 0, 0);
+          for (int t = 0; t < 9; ++t) part[t] = mma(a[y + 2 - t / 3], b[t % 3], part[t]);
+          if (dz == 1) {  // biases, as below
+            const __bf16 one = (__bf16)(y0 + y < g.ny && z0 + wave < g.nz ? 1.0f : 0.0f);
+            part[9] = mma(a[y + 1], bf16x8{one, one, one, one, one, one, one, one}, part[9]);
           }
-      // biases: the tile's own G rows (dz = dy = 1) times one, times zero for a row beyond the grid
-      const __bf16 one = (__bf16)(y0 + y < g.ny && z0 + wave < g.nz ? 1.0f : 0.0f);
-      const bf16x8 ones = {one, one, one, one, one, one, one, one};
-      acc[27] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][y + 1], ones, acc[27], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < (dz == 1 ? 10 : 9); ++t)
+#pragma unroll
+          for (int r = 0; r < KEEP; ++r) acc[t < 9 ? 9 * dz + t : 27][r] += part[t][r];
+      }
+    } else {
+      bf16x8 a[3][WTY + 2];
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) a[dz][r] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + r) * WTX * 16, lane);
+#pragma unroll
+      for (int y = 0; y < WTY; ++y) {
+        bf16x8 b[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) b[dx] = read_row_tr(xs + ((wave * WTY + y) * (WTX + 2) + dx) * 16, lane);
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+          a[dz][y + 2] = read_row_tr(gs + ((wave + 2 - dz) * (WTY + 2) + y + 2) * WTX * 16, lane);
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+              const int t = 9 * dz + 3 * dy + dx;
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[dz][y + 2 - dy], b[dx], acc[t], 0, 0, 0);
+            }
+        // biases: the tile's own G rows (dz = dy = 1) times one, times zero for a row beyond the grid
+        const __bf16 one = (__bf16)(y0 + y < g.ny && z0 + wave < g.nz ? 1.0f : 0.0f);
+        const bf16x8 ones = {one, one, one, one, one, one, one, one};
+        acc[27] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][y + 1], ones, acc[27], 0, 0, 0);
+      }
     }
   }
-  // add the four waves in a fixed order; D layout: acc[t][r] = dW[co = 4 (lane >> 4) + r][ci = lane & 15]
+  // add the four waves in a fixed order
   float* red = (float*)st;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
@@ -637,7 +688,7 @@ __global__ __launch_bounds__(256, CIS * COS == 256 ? 1 : 2) void wgrad_partial(c
     const int t = j < COS * CIS * 27 ? j % 27 : 27;
     const int co = j < COS * CIS * 27 ? j / (27 * CIS) : j - COS * CIS * 27;
     const int ci = j < COS * CIS * 27 ? (j / 27) % CIS : 0;
-    row[j] = red[(t * 65 + (co >> 2) * 16 + ci) * 4 + (co & 3)];
+    row[j] = red[CIS == 2 ? (t * 65 + co) * 4 + ci : (t * 65 + (co >> 2) * 16 + ci) * 4 + (co & 3)];
   }
 }
 
