@@ -1092,8 +1092,9 @@ extern "C" int tbs_transform_interp(tbs_ctx* c, const double* samples, double* c
       result = TBS_OK;
       break;
     }
-    // near FP64 precision the residual is its own rounding, and rtol may be below that: no further gain
-    const bool at_rounding = rtol > 0.0 && nit > 1 && rel <= 1e-14 && rel >= 0.5 * before;
+    // a solve reduces the residual to its own rounding; that grows with the coefficients, which are up to 420
+    // times the samples (degree 5, alternating signs), and rtol may be below it: no further gain
+    const bool at_rounding = rtol > 0.0 && nit > 1 && rel >= 0.5 * before;
     if (s.out <= rtol * rtol * s.out2 || at_rounding) { result = TBS_OK; break; }
     if (nit >= max_iter) { result = TBS_W_NOT_CONVERGED; break; }
     before = rel;
