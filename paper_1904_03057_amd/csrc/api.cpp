@@ -1063,7 +1063,9 @@ extern "C" int tbs_transform_interp(tbs_ctx* c, const double* samples, double* c
   int rc = need_ws(c, TBS_PREC_FP64);
   if (rc) return rc;
   c->cg_active = 0;
-  double* r = (double*)(c->ws + layout(c, TBS_PREC_FP64).off[1]);
+  const Layout L = layout(c, TBS_PREC_FP64);
+  double* r = (double*)(c->ws + L.off[1]);
+  double* tmp = (double*)(c->ws + L.off[2]);
   const BandFactor f = band_factor(c->taps.m, c->n);
   const int dims[3] = {(int)c->nx, (int)c->ny, (int)c->nz};
   int nit = 0, result;
@@ -1098,7 +1100,7 @@ extern "C" int tbs_transform_interp(tbs_ctx* c, const double* samples, double* c
     if (s.out <= rtol * rtol * s.out2 || at_rounding) { result = TBS_OK; break; }
     if (nit >= max_iter) { result = TBS_W_NOT_CONVERGED; break; }
     before = rel;
-    HIPCHK(launch_band_solve(r, coef, dims, c->n, c->bc == TBS_BC_PERIODIC, f, c->st));
+    HIPCHK(launch_band_solve(r, tmp, coef, dims, c->n, c->bc == TBS_BC_PERIODIC, f, c->st));
   }
   if (iters) *iters = nit;
   if (rel_res) *rel_res = rel;

@@ -16,8 +16,9 @@ BandFactor band_factor(const double* b, int W);
 
 // v <- (E^-1 along each of the three axes) v for v[z][y][x], E the Toeplitz band of half-width W
 // (truncated at both ends, or circulant); the last axis adds its result to dst instead of storing it
-// in v, which is left with intermediate values.  One launch per axis.
-hipError_t launch_band_solve(double* v, double* dst, const int dims[3], int W, int periodic, const BandFactor& f,
-                             hipStream_t st);
+// in v, which is left with intermediate values.  tmp: an array like v.  One launch per axis, two where its
+// lines are cut into segments.
+hipError_t launch_band_solve(double* v, double* tmp, double* dst, const int dims[3], int W, int periodic,
+                             const BandFactor& f, hipStream_t st);
 
 }  // namespace tbs

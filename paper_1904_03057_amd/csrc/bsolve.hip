@@ -230,6 +230,124 @@ __global__ __launch_bounds__(64) void solve_x(double* __restrict__ v, int64_t li
   }
 }
 
+// Thin boxes: few, long lines would leave the chip to a handful of waves, each one serial chain (the cubic 1048576 x 5 x 5
+// transform: 131 ms with whole lines, 26 with CG, 1.6 as here; 8192 x 16 x 16: 1.34, 2.4 and 0.20 ms).  There
+// each line is cut into segments that run in threads of their own: a recursion started kWarm samples before its
+// segment holds the line's values, as on a circulant line; outside a truncated line the samples are zero and so
+// are the recursions.  A segment reads its neighbours' values, so the forward and the backward recursion are two
+// launches, from one array to another.
+
+// One step of a segment's forward (BWD: backward) recursion; i: position from the segment's start (uniform).
+template <int W, bool PER, bool BWD> struct SegStep {
+  const BandFactor& f;
+  bool first;  // the line's first segment, whose rows the table holds
+  double v1, v2;
+  __device__ double co(const double* tab, int r, bool t) const {
+    return t && first ? tab[min(max(r, 0), kBandTab - 1)] : tab[kBandTab - 1];
+  }
+  __device__ double operator()(double s, int i) {
+    const bool t = !PER && i < kBandTab;
+    double y = __builtin_fma(-co(f.l1, BWD ? i + 1 : i, t), v1, s);
+    if (W == 2) y = __builtin_fma(-co(f.l2, BWD ? i + 2 : i, t), v2, y);
+    v2 = v1;
+    v1 = y;
+    return BWD ? y : y * co(f.dinv, i, t);
+  }
+};
+
+// Segments of lines along y or z (as solve_strided), blockIdx.y the segment.  add: dst += instead of dst =.
+template <int W, bool PER, bool BWD>
+__global__ __launch_bounds__(64) void seg_strided(const double* __restrict__ src, double* __restrict__ dst, int add,
+                                                  int64_t lines, int64_t inner, int64_t outer, int64_t stride, int n,
+                                                  int len, BandFactor f) {
+  const int64_t k = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (k >= lines) return;
+  const int64_t base = k / inner * outer + k % inner;
+  const int lo = blockIdx.y * len, own = min(len, n - lo), steps = kWarm<W> + own;
+  SegStep<W, PER, BWD> step{f, lo == 0, 0.0, 0.0};
+  auto pos = [&](int s) { return BWD ? own - 1 + kWarm<W> - s : s - kWarm<W>; };  // from the segment's start
+  auto load = [&](int s) -> double {
+    int i = lo + pos(min(s, steps - 1));
+    if (PER) i = i < 0 ? i + n : (i >= n ? i - n : i);
+    return i >= 0 && i < n ? src[base + (int64_t)i * stride] : 0.0;
+  };
+  double cur[kBatch], nxt[kBatch];
+#pragma unroll
+  for (int j = 0; j < kBatch; ++j) cur[j] = load(j);
+  for (int s0 = 0; s0 < steps; s0 += kBatch) {
+    double old[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      nxt[j] = load(s0 + kBatch + j);
+      const int s = s0 + j;
+      old[j] = add && s >= kWarm<W> && s < steps ? dst[base + (int64_t)(lo + pos(s)) * stride] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int s = s0 + j;
+      const double v = step(cur[j], pos(s));
+      if (s >= kWarm<W> && s < steps) dst[base + (int64_t)(lo + pos(s)) * stride] = old[j] + v;
+      cur[j] = nxt[j];
+    }
+  }
+}
+
+// Segments of lines along x: one wave per 64 of them (as solve_x), nseg consecutive ones to a line; len is a
+// multiple of kTile.
+template <int W, bool PER, bool BWD>
+__global__ __launch_bounds__(64) void seg_x(const double* __restrict__ src, double* __restrict__ dst, int64_t segs, int n,
+                                            int nseg, int len, BandFactor f) {
+  constexpr int LEAD = (kWarm<W> + kTile - 1) / kTile * kTile;
+  __shared__ double t[64][kTile + 1];
+  const int lane = threadIdx.x, lr = lane >> 5, lc = lane & 31;
+  const int64_t k0 = (int64_t)blockIdx.x * 64;
+  const int64_t line0 = (k0 + lr) / nseg;
+  const int seg0 = (int)((k0 + lr) % nseg);
+  SegStep<W, PER, BWD> step{f, (k0 + lane) % nseg == 0, 0.0, 0.0};
+  // every second segment from k0 + lr: element of column c0 + lc, -1 outside the line
+  auto each = [&](int c0, auto&& use) {
+    int64_t line = line0;
+    int seg = seg0;
+#pragma unroll
+    for (int j = 0; j < kTile; ++j) {
+      use(j, line, k0 + 2 * j + lr < segs ? seg * len + c0 + lc : -1);
+      seg += 2;
+      if (seg >= nseg) {
+        seg -= nseg;
+        ++line;
+      }
+    }
+  };
+  double pre[kTile];
+  auto fetch = [&](int c0) {
+    each(c0, [&](int j, int64_t line, int i) {
+      if (PER && k0 + 2 * j + lr < segs) i = i < 0 ? i + n : (i >= n ? i - n : i);
+      pre[j] = i >= 0 && i < n ? src[line * n + i] : 0.0;
+    });
+  };
+  const int c_first = BWD ? len - kTile + LEAD : -LEAD, c_step = BWD ? -kTile : kTile;
+  const int tiles = (len + LEAD) / kTile;
+  fetch(c_first);
+  for (int b = 0; b < tiles; ++b) {
+    const int c0 = c_first + b * c_step;
+#pragma unroll
+    for (int j = 0; j < kTile; ++j) t[2 * j + lr][lc] = pre[j];
+    __syncthreads();
+    if (b + 1 < tiles) fetch(c0 + c_step);
+#pragma unroll
+    for (int j = 0; j < kTile; ++j) {
+      const int c = BWD ? kTile - 1 - j : j;
+      t[lane][c] = step(t[lane][c], c0 + c);
+    }
+    __syncthreads();
+    if (c0 >= 0 && c0 < len)
+      each(c0, [&](int j, int64_t line, int i) {
+        if (i >= 0 && i < n) dst[line * n + i] = t[2 * j + lr][lc];
+      });
+    __syncthreads();
+  }
+}
+
 BandFactor band_factor(const double* b, int W) {
   BandFactor f{};
   double d[kBandTab];
@@ -244,22 +362,54 @@ BandFactor band_factor(const double* b, int W) {
   return f;
 }
 
+// Segments a line of n samples is cut into (1: solved whole) and their length.  kFewWaves waves are one per CU, below
+// which whole lines leave CUs idle (2048 x 32 x 32, 16 waves: 0.42 ms whole, 0.21 cut; 8192 x 64 x 64, 64 waves: 2.1 and
+// 1.2); segments of at least kMinSeg samples keep the lead-in small beside them.
+constexpr int64_t kFewWaves = 256, kManyWaves = 1024;
+constexpr int kMinSeg = 256;
+static int cut(int64_t lines, int n, int* len) {
+  const int64_t waves = (lines + 63) / 64;
+  int64_t nseg = waves < kFewWaves ? std::min<int64_t>(n / kMinSeg, (kManyWaves + waves - 1) / waves) : 1;
+  if (nseg < 2) return 1;
+  *len = (int)(((n + nseg - 1) / nseg + kTile - 1) / kTile * kTile);
+  return (n + *len - 1) / *len;
+}
+
 template <int W, bool PER>
-static hipError_t solve_axes(double* v, double* dst, const int dims[3], const BandFactor& f, hipStream_t st) {
+static hipError_t solve_axes(double* v, double* tmp, double* dst, const int dims[3], const BandFactor& f, hipStream_t st) {
   const int64_t nx = dims[0], ny = dims[1], nz = dims[2];
-  auto blocks = [](int64_t lines) { return dim3((unsigned)((lines + 63) / 64)); };
-  hipLaunchKernelGGL((solve_x<W, PER>), blocks(ny * nz), dim3(64), 0, st, v, ny * nz, (int)nx, f);
-  hipLaunchKernelGGL((solve_strided<W, PER>), blocks(nx * nz), dim3(64), 0, st, v, (double*)nullptr, nx * nz, nx,
-                     nx * ny, nx, (int)ny, f);
-  hipLaunchKernelGGL((solve_strided<W, PER>), blocks(nx * ny), dim3(64), 0, st, v, dst, nx * ny, nx * ny, (int64_t)0,
-                     nx * ny, (int)nz, f);
+  auto blocks = [](int64_t lines) { return (unsigned)((lines + 63) / 64); };
+  int len = 0;
+  if (const int nseg = cut(ny * nz, (int)nx, &len); nseg > 1) {
+    const int64_t segs = ny * nz * nseg;
+    hipLaunchKernelGGL((seg_x<W, PER, false>), dim3(blocks(segs)), dim3(64), 0, st, (const double*)v, tmp, segs, (int)nx,
+                       nseg, len, f);
+    hipLaunchKernelGGL((seg_x<W, PER, true>), dim3(blocks(segs)), dim3(64), 0, st, (const double*)tmp, v, segs, (int)nx,
+                       nseg, len, f);
+  } else {
+    hipLaunchKernelGGL((solve_x<W, PER>), dim3(blocks(ny * nz)), dim3(64), 0, st, v, ny * nz, (int)nx, f);
+  }
+  auto strided = [&](double* out, int64_t lines, int64_t inner, int64_t outer, int64_t stride, int n) {
+    if (const int nseg = cut(lines, n, &len); nseg > 1) {
+      const dim3 grid(blocks(lines), (unsigned)nseg);
+      hipLaunchKernelGGL((seg_strided<W, PER, false>), grid, dim3(64), 0, st, (const double*)v, tmp, 0, lines, inner, outer,
+                         stride, n, len, f);
+      hipLaunchKernelGGL((seg_strided<W, PER, true>), grid, dim3(64), 0, st, (const double*)tmp, out ? out : v,
+                         out ? 1 : 0, lines, inner, outer, stride, n, len, f);
+    } else {
+      hipLaunchKernelGGL((solve_strided<W, PER>), dim3(blocks(lines)), dim3(64), 0, st, v, out, lines, inner, outer, stride,
+                         n, f);
+    }
+  };
+  strided(nullptr, nx * nz, nx, nx * ny, nx, (int)ny);
+  strided(dst, nx * ny, nx * ny, 0, nx * ny, (int)nz);
   return hipGetLastError();
 }
 
-hipError_t launch_band_solve(double* v, double* dst, const int dims[3], int W, int periodic, const BandFactor& f,
-                             hipStream_t st) {
-  if (W == 1) return periodic ? solve_axes<1, true>(v, dst, dims, f, st) : solve_axes<1, false>(v, dst, dims, f, st);
-  if (W == 2) return periodic ? solve_axes<2, true>(v, dst, dims, f, st) : solve_axes<2, false>(v, dst, dims, f, st);
+hipError_t launch_band_solve(double* v, double* tmp, double* dst, const int dims[3], int W, int periodic,
+                             const BandFactor& f, hipStream_t st) {
+  if (W == 1) return periodic ? solve_axes<1, true>(v, tmp, dst, dims, f, st) : solve_axes<1, false>(v, tmp, dst, dims, f, st);
+  if (W == 2) return periodic ? solve_axes<2, true>(v, tmp, dst, dims, f, st) : solve_axes<2, false>(v, tmp, dst, dims, f, st);
   return hipErrorInvalidValue;
 }
 
