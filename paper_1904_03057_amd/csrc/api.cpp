@@ -210,7 +210,7 @@ static void plan_geometry(tbs_ctx* c, int zchunk) {
     if (f64) {
       c->dots_zc = 0;
       if (c->bc == TBS_BC_ROBIN && c->n >= 2 && zchunk == 0) {
-        const int dz = robin_dots_zc(c->nx, c->ny, c->nz, c->n);
+        const int dz = long_zc(c->nx, c->ny, c->nz, c->n);
         if (robin_dots_apart(c->nx, c->ny, c->nz, c->n, c->cgf_zc[1])) c->dots_zc = dz;
         else c->cgf_zc[1] = dz;
       }

@@ -124,14 +124,35 @@ constexpr double stencil_latency_load(int mode, int compute_bytes) {
 }
 int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks, double lat, double tail,
             double* cost = nullptr);
+// Chunks of at least 4 (2n+1) planes for about 8192 workgroups: what a launch takes where the plan is not worth it.
+int long_zc(int64_t nx, int64_t ny, int64_t nz, int n);
+// The estimate is good to about 10 % only, and one latency load per kernel is a mean over degrees and grids: the
+// light kernels (low degrees, FP32) hide more latency in more workgroups, and the plan, long chunks at just that
+// load, lost to long_zc by more than 3 % on one launch in eight (FP64) to two in three (FP32 right-hand side: 512^3
+// linear 281 against 218 us, 385x259x201 64 against 37; FP32 apply 16x2048x2048 linear 380 against 240; two-kernel
+// FP32 CG there 929 against 651).  So the plan stands only where it is kPlanGain cheaper with this load too.  Of
+// 488 launches (ten grids, degrees 1 to 5), 6 % are then more than 3 % behind long_zc (the worst 1.21) and 3 % more
+// than 3 % behind the plan (1.12).
+constexpr double kPlanGain = 0.95;
+constexpr double clamp_load(double v, double lo, double hi) { return v < lo ? lo : (v > hi ? hi : v); }
+constexpr double stencil_settled_load(int mode, int compute_bytes, int n, int bc) {
+  const double heavy = 0.3 * (n + (bc == BC_ROBIN ? 2 : 0));  // more arithmetic per plane, less latency to hide
+  if (compute_bytes == 8) return clamp_load((mode == M_CG1 ? 2.0 : 2.5) - heavy, 1.0, 2.0);
+  return mode == M_APPLY ? clamp_load(3.25 - heavy, 1.75, 3.25) : (mode == M_CG1 ? 2.4 : 4.0 - 0.3 * n);
+}
+// The linear FP64 kernels are bound by memory traffic, of which a tile that overhangs the grid has less: their
+// latency loads grow by this (fill: the share of the tiles inside the grid).  One-kernel CG iteration 16x2048x2048
+// 1206 against 1565 us, 16x16x8192 47 against 55; FP64 apply 16x2048x2048 510 against 617.
+constexpr double stencil_fill_factor(double root_fill, int compute_bytes, int n) {
+  return compute_bytes == 8 && n == 1 && root_fill < 0.9 ? 0.9 / root_fill : 1.0;
+}
 // FP64 CG on a Robin box of degree 2 or more: its nearly empty corner functions take hundreds to thousands
 // of iterations, and sums grouped in another way moved its solutions by up to 4e-8 of their RMS.  So its
-// sums keep the grouping of chunks of at least 4 (2n+1) planes (about 8192 workgroups).  Where the plan's own
-// chunks are faster by more than kRobinDotsGain, the iteration runs with those and leaves the sums to a
-// second launch that adds them in that grouping (cg_dots_kernel, which reads r, p and q again): cubic
-// 121x104x90, 36 + 22 us per iteration against 105 with the long chunks.
+// sums keep the grouping of long_zc.  Where the plan's own chunks are faster by more than kRobinDotsGain, the
+// iteration runs with those and leaves the sums to a second launch that adds them in that grouping
+// (cg_dots_kernel, which reads r, p and q again): cubic 121x104x90, 36 + 22 us per iteration against 105 with
+// the long chunks.
 constexpr double kRobinDotsGain = 1.7;
-int robin_dots_zc(int64_t nx, int64_t ny, int64_t nz, int n);
 bool robin_dots_apart(int64_t nx, int64_t ny, int64_t nz, int n, int zc);
 // zchunk > 0: the caller's own chunk length.  *shape (M_CGF): the shape the plan takes, the one with the
 // smallest cost times its time per plane (0 with a caller's chunk length).

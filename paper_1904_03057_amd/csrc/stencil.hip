@@ -54,9 +54,9 @@ int plan_zc(int64_t tiles, int64_t nz, int halo, int slots, int64_t most_blocks,
   return (int)best;
 }
 
-int robin_dots_zc(int64_t nx, int64_t ny, int64_t nz, int n) {
-  const int64_t plan_tiles = ((nx + 63) / 64) * ((ny + 15) / 16);
-  const int64_t chunks = std::max<int64_t>(1, std::min((8192 + plan_tiles - 1) / plan_tiles, nz / (4 * (2 * n + 1))));
+int long_zc(int64_t nx, int64_t ny, int64_t nz, int n) {
+  const int64_t tiles = ((nx + 63) / 64) * ((ny + 15) / 16), least = std::max(16, 4 * (2 * n + 1));
+  const int64_t chunks = std::max<int64_t>(1, std::min((8192 + tiles - 1) / tiles, nz / least));
   return (int)((nz + chunks - 1) / chunks);
 }
 
@@ -64,7 +64,7 @@ bool robin_dots_apart(int64_t nx, int64_t ny, int64_t nz, int n, int zc) {
   const int ty = stencil_tile_y(M_CGF, 8, n, BC_ROBIN);
   const int64_t tiles = ((nx + 63) / 64) * ((ny + ty - 1) / ty);
   const double lat = stencil_latency_load(M_CGF, 8);
-  return chunk_cost(tiles, nz, robin_dots_zc(nx, ny, nz, n), 2 * n, 256, lat, 0.75) >
+  return chunk_cost(tiles, nz, long_zc(nx, ny, nz, n), 2 * n, 256, lat, 0.75) >
          kRobinDotsGain * chunk_cost(tiles, nz, zc, 2 * n, 256, lat, 0.75);
 }
 
@@ -74,15 +74,23 @@ int stencil_plan_zc(int64_t nx, int64_t ny, int64_t nz, int mode, int compute_by
   if (zchunk > 0) return (int)std::min<int64_t>(zchunk, nz);
   const int wx = (mode == M_APPLY && compute_bytes == 4) ? STENCIL_APPLY_WX : 1;
   const int64_t tiles_x = (nx + 64 * wx - 1) / (64 * wx);
-  if (compute_bytes == 8 && mode == M_CG1 && bc == BC_ROBIN && n >= 2) return robin_dots_zc(nx, ny, nz, n);
+  if (compute_bytes == 8 && mode == M_CG1 && bc == BC_ROBIN && n >= 2) return long_zc(nx, ny, nz, n);
   int zc = 0;
   double least = 0.0;
   for (int sh = 0; sh < (mode == M_CGF && shape ? kCgfShapes : 1); ++sh) {
     const int ty = stencil_tile_y(mode, compute_bytes, n, bc, sh);
     if (ty == 0) continue;
+    const int64_t tiles = tiles_x * ((ny + ty - 1) / ty);
+    const double fill = stencil_fill_factor(std::sqrt((double)nx * ny / (64.0 * ty * tiles)), compute_bytes, n);
+    const double lat = stencil_latency_load(mode, compute_bytes) * (mode == M_CGF ? fill : 1.0);
     double cost;
-    const int z = plan_zc(tiles_x * ((ny + ty - 1) / ty), nz, 2 * n, 256, 16384, stencil_latency_load(mode, compute_bytes),
-                          mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75, &cost);
+    int z = plan_zc(tiles, nz, 2 * n, 256, 16384, lat, mode == M_APPLY && compute_bytes == 4 ? 1.5 : 0.75, &cost);
+    if (mode != M_CGF) {
+      const int zl = long_zc(nx, ny, nz, n);
+      const double load = stencil_settled_load(mode, compute_bytes, n, bc) * fill;
+      if (chunk_cost(tiles, nz, z, 2 * n, 256, load, 0.75) > kPlanGain * chunk_cost(tiles, nz, zl, 2 * n, 256, load, 0.75))
+        z = zl;
+    }
     cost *= cgf_plane_time(sh, compute_bytes);
     if (zc == 0 || cost < least) {
       zc = z;
