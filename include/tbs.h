@@ -227,7 +227,7 @@ int tbs_residual(tbs_ctx* ctx, const double* x, const double* b, void* r, int r_
  * events) and does not synchronise: asynchronous on the context's stream, whose device must be
  * the current one.  TBS_E_INVAL if the residual launch of this grid needs more than
  * TBS_NOALLOC_MAX_BLOCKS workgroups (its launch has ceil(Nx/64) * ceil(Ny/16) * z-chunks of them;
- * roughly an x-y plane above 3e7 points, or a small tbs_opts.zchunk).  Every call on one GPU
+ * roughly an x-y plane above 6.7e7 points, or a small tbs_opts.zchunk).  Every call on one GPU
  * uses that GPU's one buffer, which keeps the last call's values: calls that overlap in time on
  * one GPU (other streams or threads) race and must be serialised by the caller. */
 #define TBS_NOALLOC_MAX_BLOCKS 65536

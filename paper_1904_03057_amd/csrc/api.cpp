@@ -1052,7 +1052,7 @@ extern "C" int tbs_transform_eval(tbs_ctx* c, const void* coef, void* samples, i
 
 // The separable inverse (bsolve.hip) applied to the FP64 residual until that meets rtol: one pass unless
 // rtol asks for the last digits.  Against FP64 CG on E (28 iterations of the 256^3 cubic transform to
-// 1e-12, 6.9 ms with the evaluation of the result): 0.59 ms, and an error of 1e-15 against 4e-12.
+// 1e-12, 6.0 ms with the evaluation of the result): 0.59 ms, and an error of 1e-15 against 4e-12.
 extern "C" int tbs_transform_interp(tbs_ctx* c, const double* samples, double* coef, double rtol, int max_iter,
                                     int* iters, double* rel_res) {
   if (!c) return set_err(TBS_E_INVAL, "null context");

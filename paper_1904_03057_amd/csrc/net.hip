@@ -9,8 +9,9 @@
 // N = 16 voxels along x, K = 2 taps x 16 input channels per instruction (27 taps padded to 30).
 // A workgroup stages its input tile (halo 1) in LDS with 16 channels per voxel and each wave
 // accumulates 16-voxel rows.  The same kernel runs the backward data pass with flipped,
-// transposed weights; the last layer has a kernel of its own (conv_last).  Weight gradients are a deterministic two-stage reduction (per-workgroup
-// partial sums on the matrix cores, then a fixed-order sum).  Optimiser: Adam on FP32 master weights.
+// transposed weights; the last layer has a kernel of its own (conv_last).  Weight gradients are a
+// deterministic two-stage reduction (per-workgroup partial sums on the matrix cores, then a
+// fixed-order sum).  Optimiser: Adam on FP32 master weights.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(256, 6) void conv_last(const uint16_t* __restrict__
 //
 // The narrow layers use 1 or 2 of an accumulator's 4 values and have more tiles to a workgroup's chain than the
 // vector-ALU form had voxels, so each tile is summed by itself and then added: error against 64 bits at
-// 128^3 9.1e-8 to 9.9e-8, 1.8e-7 to 2.0e-7 with one chain per workgroup (38 and 39 us), 1.0e-7 to 1.2e-7 in the
+// 128^3 9.1e-8 to 9.9e-8, 1.8e-7 to 2.0e-7 with one chain per workgroup (38 and 42 us), 1.0e-7 to 1.2e-7 in the
 // vector-ALU form.
 //
 // Each workgroup sums its tiles (grid stride) in registers and writes one row of partial sums (its
@@ -793,8 +794,6 @@ __global__ __launch_bounds__(256) void mse_grad(const float* __restrict__ o, con
   if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One full pass B = Bx By Bz of the binomial low-pass on a 32 x 8 x 8 output tile staged with a
-// one-voxel halo in LDS (the three separable passes share the tile).
 // One pass of the separable binomial low-pass [1/4, 1/2, 1/4] along x, then y, then z (zero
 // fill outside a Dirichlet box, wrap-around on a periodic one).  A workgroup owns a 64 x 16
 // column of outputs and marches through a chunk of z-planes: each input plane is staged with its

@@ -2,9 +2,6 @@
 #pragma once
 #include "common.h"
 
-#ifndef STENCIL_TY
-#define STENCIL_TY 16
-#endif
 #ifndef STENCIL_APPLY_WX
 #define STENCIL_APPLY_WX 1
 #endif
@@ -30,8 +27,6 @@
 
 namespace tbs {
 
-constexpr int kTileX = 64;
-constexpr int imin(int a, int b) { return a < b ? a : b; }
 constexpr int kLdsMax = 160 * 1024;  // LDS one workgroup may hold on gfx950
 
 // LDS of the one-kernel CG iteration (degree n, tile height ty, 64 columns, es-byte compute type):
@@ -96,8 +91,8 @@ constexpr int stencil_tile_wy(int mode, int compute_bytes, int n, int bc, int sh
 }
 // Columns per lane of the x-pass.  Two: the LDS reads of a row drop from 2N + 1 values per output to
 // N + 1 or N + 2 per two outputs (in pairs), which is what bounds the FP64 kernels of high degree and
-// saves instruction slots in FP32: measured FP64 apply, quartic 385x259x201, 152 against 178 us, FP32 apply
-// cubic 928^3 1.88 against 1.95 ms, FP64 CG iteration quadratic 400^3 762 against 833 us.  One where
+// saves instruction slots in FP32: measured FP64 apply, quartic 385x259x201, 144 against 168 us, FP32 apply
+// cubic 928^3 1.69 against 1.74 ms, FP64 CG iteration quadratic 400^3 762 against 833 us.  One where
 // the pairs read no less (linear) or the copy rate already bounds the launch (FP64 quadratic apply 308
 // against 294 us, residual 425 against 405 us at 400^3).
 constexpr int stencil_x_cols(int mode, int compute_bytes, int n) {
