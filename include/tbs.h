@@ -297,7 +297,8 @@ int tbs_transform_eval(tbs_ctx* ctx, const void* coef, void* samples, int dtype)
 
 /* Direct transform: solves E coef = samples in FP64, stopping when the residual satisfies
  * ||samples - E coef|| <= rtol ||samples|| (or, for rtol > 0, when it has reached its rounding level),
- * starting from the values coef holds on entry (a copy of the samples is a good start).  *iters and
+ * starting from the values coef holds on entry (a copy of the samples is a good start).  Samples that are
+ * all zero give zero coefficients, with 0 solves and a relative residual of 0.  *iters and
  * *rel_res (nullable) receive the number of separable solves (at most max_iter; one usually does) and the
  * FP64 relative residual at exit (near FP64 precision it can exceed rtol slightly).  Synchronises.
  * Returns TBS_OK, TBS_W_NOT_CONVERGED or TBS_E_BREAKDOWN (non-finite values). */

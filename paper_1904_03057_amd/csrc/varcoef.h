@@ -43,8 +43,8 @@ constexpr int kVcWaves = 4;  // waves of a strip, one z-point of a cell each at 
 // Measured, cubic: FP32 400^3 14.8 ms with 16 rows, 17.2 with 8.
 constexpr int vc_tile_y(int dt) { return dt == 0 ? 8 : 16; }
 // z-chunk plan (plan_zc): workgroups per CU below which the latency of a wave's march counts.  Two, eight
-// waves per CU: at 192^3 cubic FP32 2.39 ms against 3.61 with one (3 gives 2.39, but 0.93 against
-// 0.81 ms at 128x100x90).
+// waves per CU.  Measured in FP32 with one / two / three: cubic 192^3 3.58 / 2.14 / 2.13 ms, 128x100x90
+// 0.93 / 0.77 / 0.88, quartic 128^3 4.07 / 3.71 / 3.49, quintic 100^3 4.70 / 5.08 / 6.74.
 constexpr double kVcLatencyLoad = 2.0;
 // Output columns of one strip: the 64 lanes hold the strip's coefficient columns and an n-column halo.
 constexpr int vc_tile_x(int n) { return 64 - 2 * n; }

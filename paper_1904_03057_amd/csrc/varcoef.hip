@@ -32,8 +32,8 @@
 // waves gives four times the waves without more halo cells, and the wave-uniform z-point keeps the
 // tables in scalar registers (cubic: 109 vector registers in FP32 and 156 in FP64; 191 and 314 in the
 // form it replaces, which gave each wave its own strip of all z-points).  Measured, against that form:
-// cubic 192^3 FP32 2.39 against 6.74 ms, FP64 3.87 against 8.38; 400^3 FP32 14.8 against 24.9, FP64 28.6
-// against 42.5; quartic 128^3 FP32 3.7 against 21.8; quintic 100^3 FP32 5.1 against 42.1.
+// cubic 192^3 FP32 2.14 against 6.70 ms, FP64 3.66 against 8.35; 400^3 FP32 14.8 against 24.7, FP64 28.6
+// against 42.4; quartic 128^3 FP32 3.7 against 21.7; quintic 100^3 FP32 5.1 against 42.0.
 #include "common.h"
 #include "varcoef.h"
 
